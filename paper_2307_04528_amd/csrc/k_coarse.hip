@@ -1,0 +1,383 @@
+// Coarsest-level solve (paper Section 2.3): `sweeps` damped block-Jacobi
+// sweeps (Eq. 1) from zero with the level held in the LDS of one block, and
+// the explicit matrix of that solve.
+//
+// A level of a few hundred columns is a serial chain of sweeps: what a sweep
+// costs is the dependent steps of its column solves and the LDS traffic of
+// its stencil. A lane owns half a column (the twisted factorisation of H_z,
+// pivots from setup): the first half of the block's wavefronts eliminates
+// the layers below the meeting layer m = nz/2 upward, the second half the
+// layers above it downward; they exchange three values per column through
+// LDS and substitute back outward. Only the iterate is read from LDS in the
+// forward pass (the four neighbours); the inverse pivots, which no sweep
+// changes, stay in registers (IPREG), as do the forward values. Two block
+// barriers per sweep: before the exchange is read (every lane has then read
+// the old neighbours, so the new iterate overwrites them in place) and after
+// the new iterate is written.
+//
+// UNIT: the block solves for U unit vectors at once, U copies of the level
+// side by side in its lanes and LDS, and writes U rows of the transposed
+// matrix. With all of its U * columns lanes packed, a block wastes no
+// wavefront on a ragged tail, and the pivots and couplings are shared. The
+// horizontal and vertical couplings are products of a layer and a row factor
+// (the metric terms separate); the row factors stay in registers and the
+// layer factors are scalar loads, so no coupling is read from LDS.
+#include "device.hpp"
+
+namespace mgk {
+
+namespace {
+using namespace dev;
+
+// Threads of a block at most (eight wavefronts, two per SIMD: a lane may use
+// 256 VGPRs, which FP64 needs for its pivots and forward values).
+constexpr int kCoarseThreads = 512;
+
+// Steps whose LDS loads are in flight ahead of the ones being solved.
+template <typename T, int NS>
+constexpr int coarse_ahead() { return std::is_same<T, float>::value && NS <= 44 ? 4 : 2; }
+
+// The LDS loads of one step: the four neighbours, and (not UNIT) the
+// right-hand side and the couplings of the layer, cn the vertical one to the
+// next layer in the half's direction.
+template <typename T>
+struct CoarseNb {
+    T w, e, s, n, f, ip, tl, ts, tn, cn;
+};
+// The LDS loads of one step of the back-substitution.
+template <typename T>
+struct CoarseBack {
+    T x, ip, cn;
+};
+
+// NS: steps compiled for; a half has more than NS - G of them, so only the
+// last G + 1 steps need a look at where its layers end.
+template <typename T, int NS, int G, bool IPREG, bool UNIT>
+__global__ __launch_bounds__(kCoarseThreads) void k_coarse_sweeps(
+    LevelView<T> L, SepView sep, const T* __restrict__ f, T* __restrict__ xout,
+    float* __restrict__ xout32, T omega, int sweeps, int U) {
+    extern __shared__ unsigned char smem_raw[];
+    const int P = int(L.plane), nz = L.nz, nJ = L.nJ, n = P * nz;
+    const int H = int(blockDim.x) >> 1;          // lanes of one half (whole wavefronts)
+    T* sx = reinterpret_cast<T*>(smem_raw);      // [U][nz][P] iterate
+    T* xch = sx + size_t(U) * n;                 // [3][H] exchange
+    T* sp = xch + 3 * H;                         // [nz][P] pivots (not IPREG)
+    T* sf = sp + (IPREG ? 0 : n);                // [nz][P] right-hand side (not UNIT)
+    T* stl = sf + (UNIT ? 0 : n);                // [nz][nJ] (not UNIT)
+    T* sth = stl + (UNIT ? 0 : nz * nJ);         // [nz][nJ+1] (not UNIT)
+    T* str = sth + (UNIT ? 0 : nz * (nJ + 1));   // [nz+1][nJ] (not UNIT)
+    for (int t = threadIdx.x; t < U * n; t += blockDim.x) sx[t] = T(0);
+    if constexpr (!IPREG)
+        for (int t = threadIdx.x; t < n; t += blockDim.x) sp[t] = L.invp[t];
+    if constexpr (!UNIT) {
+        for (int t = threadIdx.x; t < n; t += blockDim.x) sf[t] = f[t];
+        for (int t = threadIdx.x; t < nz * nJ; t += blockDim.x) stl[t] = L.Tlam[t];
+        for (int t = threadIdx.x; t < nz * (nJ + 1); t += blockDim.x) sth[t] = L.Tth[t];
+        for (int t = threadIdx.x; t < (nz + 1) * nJ; t += blockDim.x) str[t] = L.Tr[t];
+    }
+
+    const bool top = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >= H ? 1 : 0) != 0;
+    const int idx = int(threadIdx.x) - (top ? H : 0);
+    const int u0 = idx / P;
+    const bool active = u0 < U;
+    const int u = active ? u0 : 0, col = active ? idx - u0 * P : 0;
+    const Nb b = neighbours<false>(uint32_t(col), L.nI, nJ);
+    const int J = b.J;
+    // UNIT: this lane's right-hand side is 1 in layer kf (none if -1)
+    const int row = int(blockIdx.x) * U + u;
+    const int kf = UNIT && row < n && row % P == col ? row / P : -1;
+    // row factors of the couplings (UNIT)
+    const T gl = UNIT ? T(sep.gl[J]) : T(0), gs = UNIT ? T(sep.gt[J]) : T(0),
+            gn = UNIT ? T(sep.gt[J + 1]) : T(0), gr = UNIT ? T(sep.gr[J]) : T(0);
+    const int m = nz >> 1;
+    const int elim = top ? nz - 1 - m : m;   // steps this half eliminates
+    const int own = top ? elim + 1 : elim;   // and the layers it writes
+    // step t is layer t (bottom) or nz-1-t (top)
+    const int k0 = top ? nz - 1 : 0, ks = top ? -1 : 1;
+    T ip[IPREG ? NS : 1];
+    if constexpr (IPREG) {
+#pragma unroll
+        for (int t = 0; t < NS; ++t) {
+            const int k = k0 + (t < own ? t : 0) * ks;
+            ip[t] = L.invp[size_t(k) * size_t(P) + col];
+        }
+    }
+    // UNIT: the layer factors by step, step t's in lane t (read back with a
+    // readlane: scalar loads in the chain would each be waited for)
+    const int lane = int(threadIdx.x & 63u);
+    const int kl = k0 + (lane < own ? lane : 0) * ks;
+    const T hv = UNIT ? T(sep.h[kl]) : T(0), vv = UNIT ? T(sep.v[top ? kl : kl + 1]) : T(0);
+    // not UNIT, FP32: couplings times pivots kept for the back-substitution
+    constexpr bool KEEPCB = !UNIT && std::is_same<T, float>::value;
+    const T keep = T(1) - omega;
+    const int xb = u * n;
+    constexpr int D = coarse_ahead<T, NS>();
+    constexpr int NC = (NS + D - 1) / D;
+    __syncthreads();
+
+    for (int s = 0; s < sweeps; ++s) {
+        // opaque copies, once per chunk, of what the steps' addresses and role
+        // decisions depend on: they are formed where they are used, not
+        // hoisted out of the loops into hundreds of registers
+        int pl = P, kb = k0, ow = own, el = elim;
+        auto opaque = [&]() { asm volatile("" : "+s"(pl), "+s"(kb), "+s"(ow), "+s"(el)); };
+        T hs = hv, vs = vv;
+        if constexpr (UNIT) asm volatile("" : "+v"(hs), "+v"(vs));
+        // steps past a half's layers load a real layer; what they compute is
+        // discarded
+        auto layer_of = [&](int t) { return kb + (t < NS - G || t < ow ? t : 0) * ks; };
+        auto fetch = [&](int t) {
+            CoarseNb<T> r;
+            const int k = layer_of(t), o = xb + k * pl;
+            r.w = sx[o + int(b.w)];
+            r.e = sx[o + int(b.e)];
+            r.s = sx[o + int(b.s)];
+            r.n = sx[o + int(b.n)];
+            if constexpr (!IPREG) r.ip = sp[k * pl + col];
+            if constexpr (!UNIT) {
+                r.f = sf[k * pl + col];
+                r.tl = stl[k * nJ + J];
+                r.ts = sth[k * (nJ + 1) + J];
+                r.tn = sth[k * (nJ + 1) + J + 1];
+                r.cn = str[(top ? k : k + 1) * nJ + J];
+            }
+            return r;
+        };
+        auto fetch_back = [&](int t) {
+            CoarseBack<T> r;
+            const int k = layer_of(t);
+            r.x = sx[xb + k * pl + col];
+            if constexpr (!IPREG) r.ip = sp[k * pl + col];
+            if constexpr (!UNIT && !KEEPCB) r.cn = str[(top ? k : k + 1) * nJ + J];
+            return r;
+        };
+        T y[NS], cb[KEEPCB ? NS : 1];
+        // y of the layer eliminated before, and its coupling to this one
+        T vp = T(0), cp = T(0), sm = T(0), im = T(0);
+        CoarseNb<T> q[2][D];
+#pragma unroll
+        for (int d = 0; d < D; ++d) q[0][d] = fetch(d);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            opaque();
+            if (c + 1 < NC) {
+#pragma unroll
+                for (int d = 0; d < D; ++d) q[(c + 1) & 1][d] = fetch((c + 1) * D + d);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                const int t = c * D + d;
+                if (t >= NS) continue;
+                const CoarseNb<T>& r = q[c & 1][d];
+                T sv, cn;
+                if constexpr (UNIT) {
+                    sv = lane_value(hs, t) * (gl * (r.w + r.e) + gs * r.s + gn * r.n) +
+                         (kb + t * ks == kf ? T(1) : T(0));
+                    cn = lane_value(vs, t) * gr;
+                } else {
+                    sv = r.f + r.tl * (r.w + r.e) + r.ts * r.s + r.tn * r.n;
+                    cn = r.cn;
+                }
+                const T p = IPREG ? ip[IPREG ? t : 0] : r.ip;
+                sv += cp * vp;
+                y[t] = sv * p;
+                if constexpr (KEEPCB) cb[t] = cn * p;
+                if (t < NS - G - 1) {
+                    vp = y[t];
+                    cp = cn;
+                } else if (t < el) {   // wave-uniform
+                    vp = y[t];
+                    cp = cn;
+                } else if (t == el) {
+                    sm = sv;
+                    im = p;
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        // meeting layer (step elim of the top half):
+        // x_m = (s_m + Tr_{m+1} y_{m+1} + Tr_m y_{m-1}) / d_m
+        if (!top) {
+            xch[idx] = cp * vp;
+        } else {
+            xch[H + idx] = sm;
+            xch[2 * H + idx] = im;
+        }
+        if constexpr (UNIT) asm volatile("" : "+v"(vs));   // formed again below, not kept
+        CoarseBack<T> rb[2][D];
+#pragma unroll
+        for (int d = 0; d < D; ++d) rb[(NC - 1) & 1][d] = fetch_back((NC - 1) * D + d);
+        __syncthreads();
+        T z = (xch[H + idx] + xch[idx]) * xch[2 * H + idx];
+        if (active) {
+#pragma unroll
+            for (int c = NC - 1; c >= 0; --c) {
+                opaque();
+                if (c > 0) {
+#pragma unroll
+                    for (int d = 0; d < D; ++d) rb[(c - 1) & 1][d] = fetch_back((c - 1) * D + d);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int d = D - 1; d >= 0; --d) {
+                    const int t = c * D + d;
+                    if (t >= NS) continue;
+                    const CoarseBack<T>& r = rb[c & 1][d];
+                    T k_;
+                    if constexpr (KEEPCB) {
+                        k_ = cb[t];
+                    } else {
+                        const T p = IPREG ? ip[IPREG ? t : 0] : r.ip;
+                        if constexpr (UNIT) k_ = lane_value(vs, t) * gr * p;
+                        else k_ = r.cn * p;
+                    }
+                    if (t < NS - G - 1 || t < el) z = y[t] + k_ * z;
+                    const T out = omega * z + keep * r.x;
+                    if (t < NS - G || t < ow) sx[xb + (kb + t * ks) * pl + col] = out;
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        __syncthreads();
+    }
+    if constexpr (UNIT) {
+        // rows blockIdx.x * U .. of the transposed matrix, n values each
+        const long long left = (long long)(n - int(blockIdx.x) * U) * n;
+        const int count = left < (long long)U * n ? int(left) : U * n;
+        const size_t base = size_t(blockIdx.x) * size_t(U) * size_t(n);
+        for (int t = threadIdx.x; t < count; t += blockDim.x) {
+            const T v = sx[t];
+            xout[base + t] = v;
+            xout32[base + t] = float(v);
+        }
+    } else {
+        for (int t = threadIdx.x; t < n; t += blockDim.x) xout[t] = sx[t];
+    }
+}
+
+inline int lanes64(long long c) { return int((c + 63) / 64 * 64); }
+
+// LDS values of a block (see the kernel's layout).
+inline size_t coarse_values(long long plane, int nJ, int nz, int U, bool ipreg, bool unit) {
+    const size_t n = size_t(plane) * size_t(nz);
+    const size_t tables =
+        unit ? 0 : size_t(nz) * nJ + size_t(nz) * (nJ + 1) + size_t(nz + 1) * nJ;
+    return size_t(U) * n + 3 * size_t(lanes64(plane * U)) + (ipreg ? 0 : n) + (unit ? 0 : n) +
+           tables;
+}
+
+// Steps NS a half column is compiled for (a step that is not a layer costs as
+// much as one that is, and role decisions only in the last steps keep the
+// others free of selects), and the range G of half columns
+// that run in it (NS - G < half <= NS).
+template <typename F>
+void with_half(int half, F&& fn) {
+    auto go = [&](auto ns, auto g) { fn(ns, g); };
+    using std::integral_constant;
+#define MG_HALF(NS, G) \
+    if (half <= NS) return go(integral_constant<int, NS>{}, integral_constant<int, G>{})
+    MG_HALF(4, 4);
+    MG_HALF(8, 4);
+    MG_HALF(12, 4);
+    MG_HALF(16, 4);
+    MG_HALF(20, 4);
+    MG_HALF(24, 4);
+    MG_HALF(28, 4);
+    MG_HALF(32, 4);
+    MG_HALF(36, 4);
+    MG_HALF(44, 8);
+    MG_HALF(54, 10);
+    MG_HALF(64, 10);
+#undef MG_HALF
+}
+
+// Pivots in registers up to 36 steps in FP64 (72 VGPRs beside as many for
+// the forward values), up to 64 in FP32.
+template <typename T>
+constexpr bool pivots_in_registers(int ns) {
+    return std::is_same<T, float>::value || ns <= 36;
+}
+template <typename T>
+bool pivots_in_registers_for(int nz) {
+    return std::is_same<T, float>::value || (nz + 1) / 2 <= 36;
+}
+
+template <typename T, int NS, int G, bool UNIT>
+bool launch(const LevelView<T>& L, const SepView& sep, const T* f, T* x, float* x32, T omega,
+            int sweeps, int U, int blocks, hipStream_t s) {
+    constexpr bool IPREG = pivots_in_registers<T>(NS);
+    const size_t lds = coarse_values(L.plane, L.nJ, L.nz, U, IPREG, UNIT) * sizeof(T);
+    if (lds > 64 * 1024 &&
+        hipFuncSetAttribute(reinterpret_cast<const void*>(&k_coarse_sweeps<T, NS, G, IPREG, UNIT>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize,
+                            int(lds)) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    k_coarse_sweeps<T, NS, G, IPREG, UNIT>
+        <<<blocks, 2 * lanes64(L.plane * U), lds, s>>>(L, sep, f, x, x32, omega, sweeps, U);
+    return true;
+}
+
+}  // namespace
+
+template <typename T>
+bool coarse_solve_fits(long long plane, int nJ, int nz, size_t max_lds) {
+    return 2 * lanes64(plane) <= kCoarseThreads &&
+           coarse_values(plane, nJ, nz, 1, pivots_in_registers_for<T>(nz), false) * sizeof(T) <=
+               max_lds;
+}
+
+template <typename T>
+bool coarse_solve(const LevelView<T>& L, const T* f, T* x, T omega, int sweeps, size_t max_lds,
+                  hipStream_t s) {
+    if (!coarse_solve_fits<T>(L.plane, L.nJ, L.nz, max_lds)) return false;
+    bool done = false;
+    with_half((L.nz + 1) / 2, [&](auto ns, auto g) {
+        done = launch<T, decltype(ns)::value, decltype(g)::value, false>(L, SepView{}, f, x, nullptr, omega, sweeps, 1,
+                                                     1, s);
+    });
+    return done;
+}
+
+// Unit vectors per block: as many as its LDS and lanes hold, but not so many
+// that fewer than two blocks per CU remain (a smaller level then spreads over
+// more CUs instead).
+static int basis_vectors(long long plane, int nJ, int nz, size_t max_lds) {
+    const long long n = plane * nz;
+    const bool ipreg = pivots_in_registers_for<double>(nz);
+    int U = 0;
+    while (2 * lanes64(plane * (U + 1)) <= kCoarseThreads &&
+           coarse_values(plane, nJ, nz, U + 1, ipreg, true) * sizeof(double) <= max_lds &&
+           (U == 0 || (U + 1) * 512LL <= n))
+        ++U;
+    return U;
+}
+
+bool coarse_basis_fits(long long plane, int nJ, int nz, size_t max_lds) {
+    return plane * nz <= kDenseCoarseMax && plane <= kDenseCoarseColumns &&
+           basis_vectors(plane, nJ, nz, max_lds) > 0;
+}
+
+bool coarse_basis(const LevelView<double>& L, const SepView& sep, double* Ct, float* Ct32,
+                  double omega, int sweeps, size_t max_lds, hipStream_t s) {
+    const long long n = L.plane * L.nz;
+    if (n < 1 || !coarse_basis_fits(L.plane, L.nJ, L.nz, max_lds)) return false;
+    const int U = basis_vectors(L.plane, L.nJ, L.nz, max_lds);
+    bool done = false;
+    with_half((L.nz + 1) / 2, [&](auto ns, auto g) {
+        done = launch<double, decltype(ns)::value, decltype(g)::value, true>(L, sep, nullptr, Ct, Ct32, omega, sweeps,
+                                                         U, int((n + U - 1) / U), s);
+    });
+    return done;
+}
+
+template bool coarse_solve_fits<float>(long long, int, int, size_t);
+template bool coarse_solve_fits<double>(long long, int, int, size_t);
+template bool coarse_solve<float>(const LevelView<float>&, const float*, float*, float, int,
+                                  size_t, hipStream_t);
+template bool coarse_solve<double>(const LevelView<double>&, const double*, double*, double, int,
+                                   size_t, hipStream_t);
+
+}  // namespace mgk

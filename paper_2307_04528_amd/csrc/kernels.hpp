@@ -69,41 +69,36 @@ void smooth(const LevelView<T>& L, const T* f, const T* xin, T* xout, T omega,
 template <typename T>
 void sweep(const LevelView<T>& L, const T* f, const T* xin, T* xout, T omega, hipStream_t s);
 
-// The whole coarsest-level solve in one launch (one block): `sweeps` sweeps
-// from zero, ping-ponging between xa and xb. Returns 0 if the result is in
-// xa, 1 if in xb. Meant for levels of at most kCoarseSolveColumns columns;
-// levels of at most kCoarseLdsColumns columns whose data fit in max_lds bytes
-// of LDS (see coarse_lds_bytes) run entirely in LDS.
-constexpr long long kCoarseSolveColumns = 4096;
-constexpr long long kCoarseLdsColumns = 128;
-template <typename T>
-int coarse_solve(const LevelView<T>& L, const T* f, T* xa, T* xb, T omega, int sweeps,
-                 size_t max_lds, hipStream_t s);
+// Layer and row factors of a level's couplings (FP64):
+// Tlam[k][J] = h[k] gl[J], Tth[k][F] = h[k] gt[F], Tr[F][J] = v[F] gr[J].
+struct SepView {
+    const double *h = nullptr, *v = nullptr, *gl = nullptr, *gt = nullptr, *gr = nullptr;
+};
 
-// LDS bytes of the one-block coarsest solve: f, pivots and iterate per cell,
-// the three coefficient tables, and the exchange slots of two wavefront
-// pairs. unit: the unit-vector solves of coarse_basis, which store no f and
-// read the two horizontal tables from global memory.
+// The whole coarsest-level solve (`sweeps` sweeps from zero, result in x) in
+// one launch of one block with the level in its LDS. Returns false,
+// launching nothing, where the level does not fit (coarse_solve_fits).
 template <typename T>
-inline size_t coarse_lds_bytes(long long plane, int nJ, int nz, bool unit = false) {
-    const size_t horiz = unit ? 0 : size_t(nz) * nJ + size_t(nz) * (nJ + 1);
-    return ((unit ? 2 : 3) * size_t(plane) * size_t(nz) + horiz + size_t(nz + 1) * nJ + 512) *
-           sizeof(T);
-}
+bool coarse_solve_fits(long long plane, int nJ, int nz, size_t max_lds);
+template <typename T>
+bool coarse_solve(const LevelView<T>& L, const T* f, T* x, T omega, int sweeps, size_t max_lds,
+                  hipStream_t s);
 
-// The coarsest-level solve (`sweeps` sweeps from zero) is a linear map
-// x = C f of the level's n cells. coarse_basis writes C^T, row by row (row j
-// is the solve applied to the j-th unit vector), in FP64 into Ct (n*n
-// values), with one block per row and the level held in LDS. Returns false,
-// launching nothing, if n > kDenseCoarseMax or the level does not fit in
-// max_lds bytes of LDS.
+// The coarsest-level solve is a linear map x = C f of the level's n cells.
+// coarse_basis writes C^T, row by row (row j is the solve applied to the
+// j-th unit vector), computed in FP64, into Ct and rounded to FP32 into Ct32
+// (n*n values each). Returns false, launching nothing, where the level has
+// more than kDenseCoarseMax cells or kDenseCoarseColumns columns or does not
+// fit in max_lds bytes of LDS (coarse_basis_fits).
 constexpr long long kDenseCoarseMax = 6144;
-bool coarse_basis(const LevelView<double>& L, double* Ct, double omega, int sweeps,
-                  size_t max_lds, hipStream_t s);
+constexpr long long kDenseCoarseColumns = 128;
+bool coarse_basis_fits(long long plane, int nJ, int nz, size_t max_lds);
+bool coarse_basis(const LevelView<double>& L, const SepView& sep, double* Ct, float* Ct32,
+                  double omega, int sweeps, size_t max_lds, hipStream_t s);
 
-// B = A^T for n x n row-major matrices (A and B distinct).
-template <typename T>
-void transpose_square(const T* A, T* B, long long n, hipStream_t s);
+// B = A^T for n x n row-major matrices (A and B distinct), and B32 the same
+// rounded to FP32.
+void transpose_square(const double* A, double* B, float* B32, long long n, hipStream_t s);
 
 // x = A f for an n x n row-major matrix: one wavefront per row, partial sums
 // in a fixed order (results are reproducible).

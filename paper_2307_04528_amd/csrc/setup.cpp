@@ -74,6 +74,20 @@ void tables(const mg_grid& g, const std::vector<double>& re,
         for (int J = 0; J < nJ; ++J)
             L.Tr[size_t(F) * nJ + J] = K * r2 * dl * sdiff[J] / (rc[F] - rc[F - 1]);
     }
+    // the layer and row factors of the tables
+    L.fh.assign(nz, 0.0);
+    L.fv.assign(nz + 1, 0.0);
+    L.flam.assign(nJ, 0.0);
+    L.fth.assign(nJ + 1, 0.0);
+    L.fr.assign(nJ, 0.0);
+    for (int k = 0; k < nz; ++k)
+        L.fh[k] = K * ((re[k + 1] * re[k + 1] - re[k] * re[k]) / 2.0) / rc[k];
+    for (int F = 1; F < nz; ++F) L.fv[F] = K * (re[F] * re[F]) / (rc[F] - rc[F - 1]);
+    for (int J = 0; J < nJ; ++J) {
+        L.flam[J] = dth[J] / (std::cos(th[J]) * dl);
+        L.fr[J] = dl * sdiff[J];
+    }
+    for (int F = 1; F < nJ; ++F) L.fth[F] = std::cos(L.edges[F]) * dl / (th[F] - th[F - 1]);
     double amax = 0;
     for (int J = 0; J < nJ; ++J) {
         double t = dth[J] / (std::cos(th[J]) * dl);

@@ -18,6 +18,8 @@ namespace mgs {
 //   Tlam[k*nJ+J]     transmissibility of each longitude face of row J
 //   Tth[k*(nJ+1)+F]  latitude face F (south of row F); 0 at the two poles
 //   Tr[F*nJ+J]       vertical face F (below layer F); 0 at bottom and top
+// The tables separate into layer and row factors (up to rounding):
+//   Tlam[k][J] = fh[k] flam[J], Tth[k][F] = fh[k] fth[F], Tr[F][J] = fv[F] fr[J]
 //
 // Maps to the next coarser level (empty on the coarsest level):
 //   crow_of[j]          coarse row of fine row j
@@ -31,6 +33,7 @@ struct Level {
     double dlam = 0;
     std::vector<double> edges;        // nJ+1 latitude edges
     std::vector<double> V, Tlam, Tth, Tr;
+    std::vector<double> fh, fv, flam, fth, fr;
     std::vector<int> crow_of, prow;
     std::vector<double> pw;
     std::vector<int> child_first, child_count, ptrow;

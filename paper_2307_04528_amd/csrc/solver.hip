@@ -52,6 +52,7 @@ struct DevLevel {
     float *Tlam32 = nullptr, *Tth32 = nullptr, *Tr32 = nullptr;
     double *M64 = nullptr, *invp64 = nullptr;
     float *M32 = nullptr, *invp32 = nullptr;
+    double *fh = nullptr, *fv = nullptr, *flam = nullptr, *fth = nullptr, *fr = nullptr;
     mgk::StepCoef<double>* sc64 = nullptr;
     mgk::StepCoef<float>* sc32 = nullptr;
     // to the next coarser level
@@ -472,17 +473,18 @@ mg_status vcycle(mg_handle* h, int l, const T* f, T** result) {
             *result = cur;
             return MG_OK;
         }
-        if (d.plane <= mgk::kCoarseSolveColumns) {
+        if (mgk::coarse_solve_fits<T>(d.plane, d.nJ, d.nz, h->max_lds)) {
             // all coarse sweeps in one single-block launch
-            int where = 0;
+            bool done = false;
             {
                 Launch g(h, MG_K_COARSE, l,
                          double(d.n) * sizeof(T) * (3.0 + 4.0 * (h->opt.coarse_sweeps - 1)));
-                where = mgk::coarse_solve<T>(view<T>(d), f, cur, nxt, T(h->opt.omega),
-                                             h->opt.coarse_sweeps, h->max_lds, h->stream);
+                done = mgk::coarse_solve<T>(view<T>(d), f, cur, T(h->opt.omega),
+                                            h->opt.coarse_sweeps, h->max_lds, h->stream);
             }
             MG_TRY(check_launch(h, "coarse_solve"));
-            *result = where == 0 ? cur : nxt;
+            if (!done) return fail(h, MG_ERR_HIP, "the coarsest-level solve was not launched");
+            *result = cur;
             return MG_OK;
         }
         MG_TRY(op_smooth<T>(h, l, f, nullptr, cur, MG_K_COARSE, h->opt.omega));
@@ -889,17 +891,14 @@ mg_status rebuild_dense(mg_handle* h) {
     D.valid = false;
     if (!D.enabled) return MG_OK;
     const DevLevel& c = h->lv.back();
-    if (!mgk::coarse_basis(view<double>(c), D.Ct64, h->opt.omega, h->opt.coarse_sweeps,
-                           h->max_lds, h->stream)) {
+    if (!mgk::coarse_basis(view<double>(c), {c.fh, c.fv, c.flam, c.fth, c.fr}, D.Ct64, D.Ct32,
+                           h->opt.omega, h->opt.coarse_sweeps, h->max_lds, h->stream)) {
         D.enabled = false;   // does not fit: keep the sweeps
         return MG_OK;
     }
     MG_TRY(check_launch(h, "coarse_basis"));
-    mgk::transpose_square<double>(D.Ct64, D.C64, D.n, h->stream);
+    mgk::transpose_square(D.Ct64, D.C64, D.C32, D.n, h->stream);
     MG_TRY(check_launch(h, "transpose"));
-    mgk::cast<double, float>(D.C64, D.C32, D.n * D.n, h->stream);
-    mgk::cast<double, float>(D.Ct64, D.Ct32, D.n * D.n, h->stream);
-    MG_TRY(check_launch(h, "cast"));
     D.sweeps = h->opt.coarse_sweeps;
     D.omega = h->opt.omega;
     D.valid = true;
@@ -961,6 +960,13 @@ mg_status build(mg_handle* h, const double* alpha) {
         MG_TRY(dalloc(h, &d.invp64, d.n));
         MG_TRY(dalloc(h, &d.M32, d.n));
         MG_TRY(dalloc(h, &d.invp32, d.n));
+        if (l + 1 == L) {   // the coarsest level's matrix
+            MG_TRY(upload(h, &d.fh, s.fh));
+            MG_TRY(upload(h, &d.fv, s.fv));
+            MG_TRY(upload(h, &d.flam, s.flam));
+            MG_TRY(upload(h, &d.fth, s.fth));
+            MG_TRY(upload(h, &d.fr, s.fr));
+        }
         if (l + 1 < L) {
             MG_TRY(upload(h, &d.crow_of, s.crow_of));
             MG_TRY(upload(h, &d.prow, s.prow));
@@ -996,8 +1002,7 @@ mg_status build(mg_handle* h, const double* alpha) {
         const DevLevel& c = h->lv.back();
         DenseCoarse& D = h->dense;
         D.n = c.n;
-        D.enabled = c.n <= mgk::kDenseCoarseMax && c.plane <= mgk::kCoarseLdsColumns &&
-                    mgk::coarse_lds_bytes<double>(c.plane, c.nJ, c.nz, true) <= h->max_lds;
+        D.enabled = mgk::coarse_basis_fits(c.plane, c.nJ, c.nz, h->max_lds);
         if (D.enabled) {
             const size_t nn = size_t(c.n) * size_t(c.n);
             MG_TRY(dalloc(h, &D.C64, nn));

@@ -197,7 +197,9 @@ enum {
  * kern_ms[c], kern_launches[c], kern_bytes[c]: with options.profile, total
  *               event-timed milliseconds, launches and algorithmic bytes per
  *               kernel class; kern_fine_* the same restricted to the finest
- *               level.
+ *               level. A launch that does two sweeps in one pass over memory
+ *               counts as two, each with half of its time and bytes (from
+ *               zero: a third for the first sweep, two for the second).
  * ms_vcycle   : with options.profile 1 or 2, device time of the V-cycles
  *               (HIP events around each one); 0 otherwise.
  * ms_residual : the same for the refinement steps (update, residual and

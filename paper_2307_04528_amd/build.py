@@ -22,7 +22,7 @@ BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libmgshell.so")
 
 SOURCES = ["setup.cpp", "k_smooth.hip", "k_sweep.hip", "k_transfer.hip", "k_residual.hip", "k_dense.hip",
-           "k_coarse.hip", "solver.hip"]
+           "k_coarse.hip", "k_sweep_pair.hip", "solver.hip"]
 ARCH = os.environ.get("MG_OFFLOAD_ARCH", "gfx950")
 
 COMMON = [
@@ -31,6 +31,11 @@ COMMON = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-I", INCLUDE, "-I", CSRC, "-Wall", "-Wno-unused-result",
 ]
+
+# Per-source flags. k_sweep_pair: a SIMD runs one wavefront's dependent steps
+# at a time, so the schedule that favours parallelism over registers is 5 %
+# faster.
+EXTRA = {"k_sweep_pair.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]}
 
 
 def _hipcc() -> str:
@@ -42,7 +47,7 @@ def _hipcc() -> str:
 
 def _compile(src: str) -> str:
     obj = os.path.join(BUILD, os.path.basename(src) + ".o")
-    cmd = [_hipcc(), *COMMON]
+    cmd = [_hipcc(), *COMMON, *EXTRA.get(src, [])]
     if src.endswith(".cpp"):
         cmd += ["-x", "hip"]
     cmd += ["-c", os.path.join(CSRC, src), "-o", obj]

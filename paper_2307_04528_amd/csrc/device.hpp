@@ -281,6 +281,16 @@ __device__ __forceinline__ double from_above(double edge, double src) {
     return __builtin_bit_cast(double, r);
 }
 
+// The same with 0 in the lane that has no source.
+__device__ __forceinline__ float from_below0(float src) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
+                                         0, __builtin_bit_cast(int, src), 0x138, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float from_above0(float src) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
+                                         0, __builtin_bit_cast(int, src), 0x130, 0xf, 0xf, true));
+}
+
 // The value of x in lane l (l wave-uniform).
 __device__ __forceinline__ float lane_value(float x, int l) {
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), l));

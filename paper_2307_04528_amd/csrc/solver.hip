@@ -72,6 +72,9 @@ struct ProfRec {
     double bytes;
     hipEvent_t a, b;
     int launches = 1;   // consecutive launches of class cls between a and b
+    // a pair of sweeps from zero in one launch: a third of the time and bytes
+    // is the first sweep's (MG_K_SMOOTH0), the rest the second's
+    bool zero_pair = false;
 };
 
 // Explicit matrix C of the coarsest-level solve (x = C f), and C^T for the
@@ -281,11 +284,15 @@ hipEvent_t next_event(mg_handle* h) {
     return h->events[h->next_event++];
 }
 
+// launches, zero_pair: see ProfRec (a launch that does two sweeps counts as
+// two).
 struct Launch {
     mg_handle* h;
     ProfRec rec{};
     bool on = false;
-    Launch(mg_handle* hh, int cls, int level, double bytes) : h(hh) {
+    Launch(mg_handle* hh, int cls, int level, double bytes, int launches = 1,
+           bool zero_pair = false)
+        : h(hh) {
         h->alg_bytes += bytes;
         // profile 1: finest level only (no events around the short coarse
         // launches); 2: every launch; 3: none (see SweepGroup)
@@ -294,6 +301,8 @@ struct Launch {
         rec.cls = cls;
         rec.level = level;
         rec.bytes = bytes;
+        rec.launches = launches;
+        rec.zero_pair = zero_pair;
         rec.a = next_event(h);
         rec.b = next_event(h);
         if (rec.a && rec.b) {
@@ -380,16 +389,24 @@ void prof_collect(mg_handle* h, mg_stats* st) {
         st->kern_ms[c] = st->kern_bytes[c] = st->kern_fine_ms[c] = st->kern_fine_bytes[c] = 0;
         st->kern_launches[c] = st->kern_fine_launches[c] = 0;
     }
+    auto add = [&](int cls, int level, double ms, double bytes, int launches) {
+        st->kern_ms[cls] += ms;
+        st->kern_bytes[cls] += bytes;
+        st->kern_launches[cls] += launches;
+        if (level == 0) {
+            st->kern_fine_ms[cls] += ms;
+            st->kern_fine_bytes[cls] += bytes;
+            st->kern_fine_launches[cls] += launches;
+        }
+    };
     for (const ProfRec& r : h->recs) {
         float ms = 0;
         if (hipEventElapsedTime(&ms, r.a, r.b) != hipSuccess) continue;
-        st->kern_ms[r.cls] += ms;
-        st->kern_bytes[r.cls] += r.bytes;
-        st->kern_launches[r.cls] += r.launches;
-        if (r.level == 0) {
-            st->kern_fine_ms[r.cls] += ms;
-            st->kern_fine_bytes[r.cls] += r.bytes;
-            st->kern_fine_launches[r.cls] += r.launches;
+        if (r.zero_pair) {
+            add(MG_K_SMOOTH0, r.level, ms / 3.0, r.bytes / 3.0, 1);
+            add(r.cls, r.level, ms * 2.0 / 3.0, r.bytes * 2.0 / 3.0, 1);
+        } else {
+            add(r.cls, r.level, ms, r.bytes, r.launches);
         }
     }
 }
@@ -416,6 +433,61 @@ mg_status op_smooth(mg_handle* h, int l, const T* f, const T* xin, T* xout, int 
         mgk::smooth<T>(view<T>(d), f, xin, xout, T(omega), h->opt.staged_columns, h->stream);
     }
     return check_launch(h, "smooth");
+}
+
+// Whether level l does its sweeps two at a time (FP32 levels that the staged
+// kernel does not take and whose rows fit the pair kernel).
+template <typename T>
+bool sweeps_in_pairs(const mg_handle* h, int l) {
+    if constexpr (std::is_same<T, float>::value) {
+        const DevLevel& d = h->lv[l];
+        return d.plane >= h->opt.staged_columns && d.plane >= mgk::kPairColumns &&
+               mgk::sweep_pair_fits(view<float>(d), h->max_lds);
+    }
+    return false;
+}
+
+// nu sweeps on level l with the damping factors of a smoothing step of nu
+// sweeps (reversed: in reverse order), from zero or from the iterate in cur;
+// the result is in cur.
+template <typename T>
+mg_status smooth_run(mg_handle* h, int l, const T* f, T*& cur, T*& nxt, int nu, bool from_zero,
+                     bool reversed) {
+    DevLevel& d = h->lv[l];
+    auto om = [&](int k) { return mgs::sweep_omega(h->opt, nu, reversed ? nu - 1 - k : k); };
+    const bool pairs = sweeps_in_pairs<T>(h, l);
+    int k = 0;
+    while (k < nu) {
+        const bool zero = from_zero && k == 0;
+        const T* xin = zero ? nullptr : cur;
+        T* xout = zero ? cur : nxt;
+        if constexpr (std::is_same<T, float>::value) {
+            if (pairs && k + 1 < nu) {
+                bool done = false;
+                {
+                    Launch g(h, MG_K_SMOOTH, l, double(d.n) * sizeof(T) * (zero ? 3 : 4), 2, zero);
+                    done = mgk::sweep_pair(view<float>(d), f, xin, xout, float(om(k)),
+                                           float(om(k + 1)), h->max_lds, h->stream);
+                }
+                MG_TRY(check_launch(h, "sweep_pair"));
+                if (!done) return fail(h, MG_ERR_HIP, "the pair of sweeps was not launched");
+                if (!zero) std::swap(cur, nxt);
+                k += 2;
+                continue;
+            }
+        }
+        MG_TRY(op_smooth<T>(h, l, f, xin, xout, zero ? MG_K_SMOOTH0 : MG_K_SMOOTH, om(k)));
+        if (!zero) std::swap(cur, nxt);
+        ++k;
+    }
+    return MG_OK;
+}
+
+// Algorithmic bytes of nu sweeps from an iterate on level l.
+template <typename T>
+double sweeps_bytes(const mg_handle* h, int l, int nu) {
+    const int passes = sweeps_in_pairs<T>(h, l) ? (nu + 1) / 2 : nu;
+    return double(passes) * double(h->lv[l].n) * sizeof(T) * 4;
 }
 
 template <typename T>
@@ -496,23 +568,15 @@ mg_status vcycle(mg_handle* h, int l, const T* f, T** result) {
         return MG_OK;
     }
     const int nu1 = h->opt.nu_pre, nu2 = h->opt.nu_post;
-    MG_TRY(op_smooth<T>(h, l, f, nullptr, cur, MG_K_SMOOTH0, mgs::sweep_omega(h->opt, nu1, 0)));
-    for (int s = 1; s < nu1; ++s) {
-        MG_TRY(op_smooth<T>(h, l, f, cur, nxt, MG_K_SMOOTH, mgs::sweep_omega(h->opt, nu1, s)));
-        std::swap(cur, nxt);
-    }
+    MG_TRY(smooth_run<T>(h, l, f, cur, nxt, nu1, true, false));
     Work<T>& wc = work<T>(h->lv[l + 1]);
     MG_TRY(op_restrict<T>(h, l, f, cur, wc.f));
     T* xc = nullptr;
     MG_TRY(vcycle<T>(h, l + 1, wc.f, &xc));
     MG_TRY(op_prolong<T>(h, l, xc, cur));
     {
-        SweepGroup g(h, l, nu2, double(nu2) * double(d.n) * sizeof(T) * 4);
-        for (int s = 0; s < nu2; ++s) {
-            MG_TRY(op_smooth<T>(h, l, f, cur, nxt, MG_K_SMOOTH,
-                                mgs::sweep_omega(h->opt, nu2, s)));
-            std::swap(cur, nxt);
-        }
+        SweepGroup g(h, l, nu2, sweeps_bytes<T>(h, l, nu2));
+        MG_TRY(smooth_run<T>(h, l, f, cur, nxt, nu2, false, false));
     }
     *result = cur;
     return MG_OK;
@@ -625,12 +689,7 @@ mg_status vcycle_adj(mg_handle* h, int l, const T* f, T** result) {
     const int nu1 = h->opt.nu_pre, nu2 = h->opt.nu_post;
     Work<T>& wc = work<T>(h->lv[l + 1]);
     if (nu2 > 0) {
-        MG_TRY(op_smooth<T>(h, l, f, nullptr, cur, MG_K_SMOOTH0,
-                            mgs::sweep_omega(h->opt, nu2, nu2 - 1)));
-        for (int s = nu2 - 2; s >= 0; --s) {
-            MG_TRY(op_smooth<T>(h, l, f, cur, nxt, MG_K_SMOOTH, mgs::sweep_omega(h->opt, nu2, s)));
-            std::swap(cur, nxt);
-        }
+        MG_TRY(smooth_run<T>(h, l, f, cur, nxt, nu2, true, true));
         MG_TRY(op_restrict_T<T>(h, l, f, cur, nxt, wc.f));
     } else {
         // no sweeps: the iterate is zero and its residual is f
@@ -647,11 +706,8 @@ mg_status vcycle_adj(mg_handle* h, int l, const T* f, T** result) {
     MG_TRY(vcycle_adj<T>(h, l + 1, wc.f, &xc));
     MG_TRY(op_inject<T>(h, l, xc, cur));
     {
-        SweepGroup g(h, l, nu1, double(nu1) * double(d.n) * sizeof(T) * 4);
-        for (int s = nu1 - 1; s >= 0; --s) {
-            MG_TRY(op_smooth<T>(h, l, f, cur, nxt, MG_K_SMOOTH, mgs::sweep_omega(h->opt, nu1, s)));
-            std::swap(cur, nxt);
-        }
+        SweepGroup g(h, l, nu1, sweeps_bytes<T>(h, l, nu1));
+        MG_TRY(smooth_run<T>(h, l, f, cur, nxt, nu1, false, true));
     }
     *result = cur;
     return MG_OK;

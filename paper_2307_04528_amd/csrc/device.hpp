@@ -364,6 +364,31 @@ void with_nz(int nz, F&& fn) {
     else fn(std::integral_constant<int, 128>{});
 }
 
+// Steps NS a half column is compiled for (a step that is not a layer costs as
+// much as one that is, and role decisions only in the last steps keep the
+// others free of selects), and the range G of half columns
+// that run in it (NS - G < half <= NS).
+template <typename F>
+void with_half(int half, F&& fn) {
+    auto go = [&](auto ns, auto g) { fn(ns, g); };
+    using std::integral_constant;
+#define MG_HALF(NS, G) \
+    if (half <= NS) return go(integral_constant<int, NS>{}, integral_constant<int, G>{})
+    MG_HALF(4, 4);
+    MG_HALF(8, 4);
+    MG_HALF(12, 4);
+    MG_HALF(16, 4);
+    MG_HALF(20, 4);
+    MG_HALF(24, 4);
+    MG_HALF(28, 4);
+    MG_HALF(32, 4);
+    MG_HALF(36, 4);
+    MG_HALF(44, 8);
+    MG_HALF(54, 10);
+    MG_HALF(64, 10);
+#undef MG_HALF
+}
+
 // Levels with fewer columns than this run their Thomas sweeps with the
 // deeper prefetch (more layers in flight per lane, fewer lanes): below
 // ~2^19 columns the GPU holds every column at once, so the per-column

@@ -21,46 +21,71 @@ using namespace dev;
 
 // Staged sweep for small levels. A level of a few thousand columns leaves
 // most of the GPU idle: a sweep then costs the critical path of one column
-// (its memory round trips and the instructions of its recurrences), not
+// (its memory round trips and the dependent steps of its solve), not
 // bandwidth. Here kStageWaves wavefronts share one segment of 64 columns:
 // wavefront w loads layers w, w + kStageWaves, ... (all of its loads in one
-// round trip), forms the right-hand sides s = f + sum_h T_h x_nb and writes
-// s, the inverse pivots, the old iterate and the row's couplings Tr to LDS.
-// After one block barrier the first two wavefronts solve the twisted
-// factorisation of H_z in rolled loops over LDS (no per-layer address or
-// branch arithmetic of a fully unrolled register solve), with the same
-// recurrences as k_sweep: the forward values y_k overwrite s_k, the
-// couplings Tr_next * ip_k overwrite the pivots.
+// round trip), forms the right-hand sides s = f + sum_h T_h x_nb and writes s
+// and the inverse pivots to LDS. After a block barrier the first two
+// wavefronts solve the twisted factorisation of H_z, a half column each: s
+// and the pivots come from LDS a chunk ahead, the row's vertical couplings
+// from the wavefront's lanes, and the forward values stay in registers, so a
+// step costs its few instructions. They leave the solution in LDS; after
+// another barrier every wavefront damps and stores its own layers, whose old
+// iterate it still holds.
+//
+// In LDS the upper half column lies from the top down after the lower one
+// from the bottom up: step t of a half is t * 64 values from the half's base.
+//
+// Measured: a launch takes 5.6 us on levels of 1-6K columns with 70 layers
+// (7.9 with the solve in rolled loops over LDS, where each step waited for
+// its loads), 4.7 with 38 layers (6.0), FP64 8.0 with 70 (11.0); 10.9 us of
+// 27,648 columns (13.0); with 100 layers, where the LDS now holds the layers
+// there are and not 128, 26 us of 51,200 columns (51.7).
 constexpr int kStageWaves = 8;
 
-// Dynamic LDS of k_smooth_staged (its static LDS holds NZ + 8 + 256 values).
-template <typename T, int NZ, bool HAS_X>
-constexpr size_t staged_lds_bytes() {
-    return sizeof(T) * size_t(HAS_X ? 3 : 2) * NZ * 64;
+__device__ __forceinline__ float fmad(float a, float b, float c) { return fmaf(a, b, c); }
+__device__ __forceinline__ double fmad(double a, double b, double c) { return fma(a, b, c); }
+
+// Dynamic LDS of k_smooth_staged: s and pivots by layer (and the rows that
+// the padded steps read), and the pair's exchange.
+template <typename T>
+constexpr size_t staged_lds_bytes(int nz, int pad) {
+    return sizeof(T) * (2 * size_t(nz + pad) * 64 + 256);
 }
 
-template <typename T, int NZ, bool HAS_X>
-__global__ __launch_bounds__(64 * kStageWaves) void k_smooth_staged(
+// NS: steps of a half column compiled for; a half has more than NS - G.
+template <typename T, int NS, int G, bool HAS_X>
+__global__ __launch_bounds__(64 * kStageWaves)
+__attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2))) void k_smooth_staged(
     LevelView<T> L, const T* __restrict__ f, const T* __restrict__ xin, T* __restrict__ xout,
     T omega, int wpr) {
+    // products and sums are contracted by hand: the same bits in every variant
+#pragma clang fp contract(off)
     extern __shared__ unsigned char smem_raw[];
-    T* ls = reinterpret_cast<T*>(smem_raw);   // [NZ][64] s_k, then y_k
-    T* lp = ls + NZ * 64;                      // [NZ][64] ip_k, then cb_k
-    T* lx = lp + NZ * 64;                      // [NZ][64] old iterate (HAS_X)
-    // separate LDS objects: the compiler then knows that the column loops'
-    // stores to ls and lp leave the couplings alone
-    __shared__ T ltr[NZ + 8];   // Tr_F of the row
-    __shared__ T xch[256];      // the pair's exchange
+    const int nz = L.nz, nJ = L.nJ, m = nz >> 1;
+    T* ls = reinterpret_cast<T*>(smem_raw);   // [nz + G][64] s, then the solution
+    T* lp = ls + (nz + G) * 64;               // [nz + G][64] inverse pivots
+    T* xch = lp + (nz + G) * 64;              // [4][64] the pair's exchange
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
     const int lane = int(threadIdx.x & 63u);
-    const Seg g = segment(int(blockIdx.x), L.nI, L.nJ, wpr);
+    const Seg g = segment(int(blockIdx.x), L.nI, nJ, wpr);
     const NbB<T> b(g);
-    const int nz = L.nz, nJ = L.nJ, J = g.J;
+    const int J = g.J;
     const uint64_t Pb = uint64_t(L.plane) * sizeof(T);
-    constexpr int Q = (NZ + kStageWaves - 1) / kStageWaves;
+    constexpr int Q = (2 * NS + kStageWaves - 1) / kStageWaves;
+    // position of layer k in LDS
+    auto pos = [&](int k) { return k < m ? k : m + (nz - 1 - k); };
+    const bool top = wave == 1;
+    // the vertical couplings of the solving wavefronts' row: lane t holds that
+    // of step t to the next layer toward the meeting layer
+    T tr = T(0);
+    if (wave < 2) {
+        int F = top ? nz - 1 - lane : lane + 1;
+        F = F < 0 ? 0 : (F < nz ? F : nz);
+        tr = L.Tr[size_t(F) * size_t(nJ) + size_t(J)];
+    }
+    T rc[HAS_X ? Q : 1];
     {
-        const int F = int(threadIdx.x);
-        const T trF = F <= nz ? L.Tr[size_t(F) * size_t(nJ) + size_t(J)] : T(0);
         // the horizontal couplings of this wavefront's layers: lane q holds
         // those of layer wave + q kStageWaves (vector loads issued with the
         // stencil loads, read back with readlane)
@@ -71,8 +96,8 @@ __global__ __launch_bounds__(64 * kStageWaves) void k_smooth_staged(
             cts = L.Tth[size_t(kq) * size_t(nJ + 1) + size_t(J)];
             ctn = L.Tth[size_t(kq) * size_t(nJ + 1) + size_t(J) + 1];
         }
-        T rf[Q], rp[Q], rc[HAS_X ? Q : 1], rw[HAS_X ? Q : 1], re[HAS_X ? Q : 1],
-            rs[HAS_X ? Q : 1], rn[HAS_X ? Q : 1];
+        T rf[Q], rp[Q], rw[HAS_X ? Q : 1], re[HAS_X ? Q : 1], rs[HAS_X ? Q : 1],
+            rn[HAS_X ? Q : 1];
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
             const int kk = clampk(wave + q * kStageWaves, nz);
@@ -88,79 +113,123 @@ __global__ __launch_bounds__(64 * kStageWaves) void k_smooth_staged(
             }
         }
         __builtin_amdgcn_sched_barrier(0);
-        if (F <= nz) ltr[F] = trF;
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
             const int k = wave + q * kStageWaves;
             if (k < nz) {
                 T s = rf[q];
                 if constexpr (HAS_X) {
-                    s += lane_value(ctl, q) * (rw[q] + re[q]) + lane_value(cts, q) * rs[q] +
-                         lane_value(ctn, q) * rn[q];
-                    lx[k * 64 + lane] = rc[q];
+                    const T h = lane_value(cts, q) * rs[q];
+                    s += fmad(lane_value(ctn, q), rn[q],
+                              fmad(lane_value(ctl, q), rw[q] + re[q], h));
                 }
-                ls[k * 64 + lane] = s;
-                lp[k * 64 + lane] = rp[q];
+                ls[pos(k) * 64 + lane] = s;
+                lp[pos(k) * 64 + lane] = rp[q];
             }
         }
     }
     __syncthreads();
-    if (wave >= 2) {
-        __syncthreads();   // the solving pair's exchange barrier
-        return;
-    }
-    const bool top = wave == 1;
-    const int m = nz >> 1;
-    const T keep = T(1) - omega;
-    // forward: bottom eliminates layers 0..m-1 upward, top nz-1..m+1 downward
-    T vp = T(0), sm = T(0), im = T(0);
-    if (!top) {
-#pragma unroll 4
-        for (int k = 0; k < m; ++k) {
-            const T s = ls[k * 64 + lane], ip = lp[k * 64 + lane];
-            const T v = (s + ltr[k] * vp) * ip;
-            ls[k * 64 + lane] = v;
-            lp[k * 64 + lane] = ltr[k + 1] * ip;
-            vp = v;
+    const int elim = top ? nz - 1 - m : m;   // steps a half eliminates
+    const int own = top ? elim + 1 : elim;   // and the layers it solves for
+    T* hs = ls + (top ? m * 64 : 0) + lane;
+    const T* hp = lp + (top ? m * 64 : 0) + lane;
+    // Couplings times pivots for the way back, kept where the registers allow.
+    // (FP32: two blocks per CU, 128 VGPRs: 26 us against 34 with one on the
+    // 51,200 columns of 100 layers. FP64 spills at 128: 20.7 us against 19.1
+    // on 23,552 columns of 70 layers.)
+    constexpr bool KEEPCB = sizeof(T) == 4 ? NS <= 44 : NS <= 36;
+    constexpr int D = sizeof(T) == 4 ? 6 : 3;
+    constexpr int NC = (NS + D - 1) / D;
+    T y[NS], cb[KEEPCB ? NS : 1];
+    if (wave < 2) {
+        T bs[2][D], bp[2][D];
+        auto fetch = [&](int c) {
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                const int t = c * D + d < NS ? c * D + d : NS - 1;
+                bs[c & 1][d] = hs[t * 64];
+                bp[c & 1][d] = hp[t * 64];
+            }
+        };
+        T vp = T(0), cp = T(0), sm = T(0), im = T(0);
+        fetch(0);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            if (c + 1 < NC) fetch(c + 1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                const int t = c * D + d;
+                if (t >= NS) continue;
+                const T s = bs[c & 1][d], ip = bp[c & 1][d], cn = lane_value(tr, t);
+                T v = fmad(cp, vp, s) * ip;
+                // computed here, not sunk (with its operands) to later blocks
+                asm volatile("" : "+v"(v));
+                y[t] = v;
+                if constexpr (KEEPCB) cb[t] = cn * ip;
+                if (t < NS - G - 1 || t < elim) {   // wave-uniform
+                    vp = v;
+                    cp = cn;
+                } else if (t == elim) {
+                    sm = s;
+                    im = ip;
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
         }
-        xch[lane] = vp;
-    } else {
-#pragma unroll 4
-        for (int k = nz - 1; k > m; --k) {
-            const T s = ls[k * 64 + lane], ip = lp[k * 64 + lane];
-            const T v = (s + ltr[k + 1] * vp) * ip;
-            ls[k * 64 + lane] = v;
-            lp[k * 64 + lane] = ltr[k] * ip;
-            vp = v;
+        if (!top) {
+            xch[lane] = vp;
+        } else {
+            xch[64 + lane] = vp;
+            xch[128 + lane] = sm;
+            xch[192 + lane] = im;
         }
-        sm = ls[m * 64 + lane];
-        im = lp[m * 64 + lane];
-        xch[64 + lane] = vp;
-        xch[128 + lane] = sm;
-        xch[192 + lane] = im;
     }
     __syncthreads();
-    // meeting layer: x_m = (s_m + Tr_m y_{m-1} + Tr_{m+1} z_{m+1}) / d_m
-    const T xm =
-        (xch[128 + lane] + ltr[m] * xch[lane] + ltr[m + 1] * xch[64 + lane]) * xch[192 + lane];
-    auto put = [&](int k, T z) {
-        T out = omega * z;
-        if constexpr (HAS_X) out += keep * lx[k * 64 + lane];
-        if (g.valid) stb<T>(layer_w(xout, k, Pb), b.c, out);
-    };
-    T xv = xm;
-    if (!top) {
-#pragma unroll 4
-        for (int k = m - 1; k >= 0; --k) {
-            xv = ls[k * 64 + lane] + lp[k * 64 + lane] * xv;
-            put(k, xv);
+    if (wave < 2) {
+        // meeting layer: x_m = (s_m + Tr_m y_{m-1} + Tr_{m+1} z_{m+1}) / d_m
+        // (the couplings' faces have no lane where a half is empty; Tr is 0)
+        const T cm = m > 0 ? L.Tr[size_t(m) * size_t(nJ) + size_t(J)] : T(0);
+        const T cm1 = m + 1 < nz ? L.Tr[size_t(m + 1) * size_t(nJ) + size_t(J)] : T(0);
+        T z = fmad(cm1, xch[64 + lane], fmad(cm, xch[lane], xch[128 + lane])) * xch[192 + lane];
+        T bp[2][KEEPCB ? 1 : D];
+        auto fetch = [&](int c) {
+            if constexpr (!KEEPCB) {
+#pragma unroll
+                for (int d = 0; d < D; ++d)
+                    bp[c & 1][d] = hp[(c * D + d < NS ? c * D + d : NS - 1) * 64];
+            }
+        };
+        fetch(NC - 1);
+#pragma unroll
+        for (int c = NC - 1; c >= 0; --c) {
+            if (c > 0) fetch(c - 1);
+            if constexpr (!KEEPCB) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int d = D - 1; d >= 0; --d) {
+                const int t = c * D + d;
+                if (t >= NS) continue;
+                T k_;
+                if constexpr (KEEPCB) k_ = cb[t];
+                else k_ = lane_value(tr, t) * bp[c & 1][d];
+                if (t < NS - G - 1 || t < elim) z = fmad(k_, z, y[t]);
+                if (t < NS - G || t < own) hs[t * 64] = z;
+            }
         }
-    } else {
-        put(m, xm);
-#pragma unroll 4
-        for (int k = m + 1; k < nz; ++k) {
-            xv = ls[k * 64 + lane] + lp[k * 64 + lane] * xv;
-            put(k, xv);
+    }
+    __syncthreads();
+    const T keep = T(1) - omega;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const int k = wave + q * kStageWaves;
+        if (k < nz) {
+            const T z = ls[pos(k) * 64 + lane];
+            T out = omega * z;
+            if constexpr (HAS_X) {
+                const T old = keep * rc[q];
+                out = fmad(omega, z, old);
+            }
+            if (g.valid) stb<T>(layer_w(xout, k, Pb), b.c, out);
         }
     }
 }
@@ -178,24 +247,22 @@ bool launch_staged(const LevelView<T>& L, const T* f, const T* xin, T* xout, T o
     const int wpr = segments_per_row(L.nI);
     const int nb = L.nJ * wpr;
     bool launched = false;
-    with_nz(L.nz, [&](auto nzc) {
-        constexpr int NZ = decltype(nzc)::value;
+    with_half((L.nz + 1) / 2, [&](auto ns, auto gc) {
+        constexpr int NS = decltype(ns)::value, G = decltype(gc)::value;
+        const size_t lds = staged_lds_bytes<T>(L.nz, G);
+        if (lds > kMaxLds) return;
         auto go = [&](auto hx) {
             constexpr bool HX = decltype(hx)::value;
-            constexpr size_t lds = staged_lds_bytes<T, NZ, HX>();
-            if constexpr (lds + sizeof(T) * (NZ + 8 + 256) <= kMaxLds) {
-                const void* fn =
-                    reinterpret_cast<const void*>(&k_smooth_staged<T, NZ, HX>);
-                if (lds > 64 * 1024 &&
-                    hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                        int(lds)) != hipSuccess) {
-                    (void)hipGetLastError();
-                    return;
-                }
-                k_smooth_staged<T, NZ, HX>
-                    <<<nb, 64 * kStageWaves, lds, s>>>(L, f, xin, xout, omega, wpr);
-                launched = true;
+            const void* fn = reinterpret_cast<const void*>(&k_smooth_staged<T, NS, G, HX>);
+            if (lds > 64 * 1024 &&
+                hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    int(lds)) != hipSuccess) {
+                (void)hipGetLastError();
+                return;
             }
+            k_smooth_staged<T, NS, G, HX>
+                <<<nb, 64 * kStageWaves, lds, s>>>(L, f, xin, xout, omega, wpr);
+            launched = true;
         };
         if (xin) go(std::true_type{});
         else go(std::false_type{});

@@ -69,7 +69,8 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse_sweeps(
     for (int t = threadIdx.x; t < U * n; t += blockDim.x) sx[t] = T(0);
     if constexpr (!IPREG)
         for (int t = threadIdx.x; t < n; t += blockDim.x) sp[t] = L.invp[t];
-    if constexpr (!UNIT) {
+    constexpr bool STAGE = !UNIT && !(std::is_same<T, float>::value && NS <= 24);
+    if constexpr (STAGE) {
         for (int t = threadIdx.x; t < n; t += blockDim.x) sf[t] = f[t];
         for (int t = threadIdx.x; t < nz * nJ; t += blockDim.x) stl[t] = L.Tlam[t];
         for (int t = threadIdx.x; t < nz * (nJ + 1); t += blockDim.x) sth[t] = L.Tth[t];
@@ -109,6 +110,22 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse_sweeps(
     const T hv = UNIT ? T(sep.h[kl]) : T(0), vv = UNIT ? T(sep.v[top ? kl : kl + 1]) : T(0);
     // not UNIT, FP32: couplings times pivots kept for the back-substitution
     constexpr bool KEEPCB = !UNIT && std::is_same<T, float>::value;
+    // not UNIT, FP32, short columns: what no sweep changes stays in registers
+    // (right-hand side and couplings), so a step reads only its neighbours
+    constexpr bool HOLD = KEEPCB && NS <= 24;
+    T hf[HOLD ? NS : 1], hl[HOLD ? NS : 1], hs_[HOLD ? NS : 1], hn[HOLD ? NS : 1],
+        hc[HOLD ? NS : 1];
+    if constexpr (HOLD) {
+#pragma unroll
+        for (int t = 0; t < NS; ++t) {
+            const int k = k0 + (t < own ? t : 0) * ks;
+            hf[t] = f[size_t(k) * size_t(P) + col];
+            hl[t] = L.Tlam[k * nJ + J];
+            hs_[t] = L.Tth[k * (nJ + 1) + J];
+            hn[t] = L.Tth[k * (nJ + 1) + J + 1];
+            hc[t] = L.Tr[(top ? k : k + 1) * nJ + J];
+        }
+    }
     const T keep = T(1) - omega;
     const int xb = u * n;
     constexpr int D = coarse_ahead<T, NS>();
@@ -134,7 +151,7 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse_sweeps(
             r.s = sx[o + int(b.s)];
             r.n = sx[o + int(b.n)];
             if constexpr (!IPREG) r.ip = sp[k * pl + col];
-            if constexpr (!UNIT) {
+            if constexpr (!UNIT && !HOLD) {
                 r.f = sf[k * pl + col];
                 r.tl = stl[k * nJ + J];
                 r.ts = sth[k * (nJ + 1) + J];
@@ -175,6 +192,10 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse_sweeps(
                     sv = lane_value(hs, t) * (gl * (r.w + r.e) + gs * r.s + gn * r.n) +
                          (kb + t * ks == kf ? T(1) : T(0));
                     cn = lane_value(vs, t) * gr;
+                } else if constexpr (HOLD) {
+                    const int h = HOLD ? t : 0;
+                    sv = hf[h] + hl[h] * (r.w + r.e) + hs_[h] * r.s + hn[h] * r.n;
+                    cn = hc[h];
                 } else {
                     sv = r.f + r.tl * (r.w + r.e) + r.ts * r.s + r.tn * r.n;
                     cn = r.cn;

@@ -9,7 +9,7 @@
 namespace mgk {
 
 constexpr int kResidualSync = 4;
-// A k_residual_update block has one wavefront per row of its tile of R
+// A k_residual_walk block has one wavefront per row of its tile of R
 // consecutive rows: R = 16 where that still gives at least
 // kResidualTallBlocks blocks, else R = 4 (small levels would leave CUs
 // idle). Every kResidualSync layers the block's wavefronts meet at a
@@ -66,6 +66,13 @@ template <typename T>
 constexpr int apply_layers() {
     return std::is_same<T, float>::value ? 2 : 4;
 }
+// In FP64 large levels take the walk of the refinement step (MODE 1 and 2) in
+// ranges of kApplyRange layers, which reads each column once per range:
+// 640x480x50 92 us against 104 for this kernel (101 with ranges of 16, 89 and
+// 358 on 1024x768x70 with whole columns), 1024x768x70 276 against 323; smaller
+// levels have too few columns for it (384x192: 45 against 41 us).
+constexpr int kApplyRange = 25;
+constexpr long long kApplyWalkColumns = 1LL << 18;
 
 // y = H x (HAS_F = false) or y = f - H x, one lane per column and chunk of
 // apply_layers layers, in blocks of 64 columns x kApplyRows rows (grid:
@@ -115,66 +122,12 @@ __global__ __launch_bounds__(64 * kApplyRows) void k_apply(LevelView<T> L,
         if (k0 + d < nz) y[size_t(k0 + d) * P + c] = hs[d];
 }
 
-// Refinement step on the finest level, one lane per column (row-tiled
-// segments, one wavefront per row of the block's tile), in the precision TU
-// of the iterate (FP64; FP32 in the pure single-precision solve):
+// Refinement step on the finest level (MODE 0), in the precision TU of the
+// iterate (FP64; FP32 in the pure single-precision solve):
 //   unew = uin + e (HAS_E; written to uout), r = b - H unew (stored as TR),
-//   per-block partial sums of r^2 in FP64, and of b^2 when partials_b is set.
-// Levels of more than 72 layers (the walking kernel below takes the others).
-template <typename TU, typename TE, typename TR, int NZ, bool HAS_E, int R>
-__global__ __launch_bounds__(64 * R) void k_residual_update(
-    LevelView<TU> L, const TU* __restrict__ bv, const TU* __restrict__ uin,
-    const TE* __restrict__ e, TU* __restrict__ uout, TR* __restrict__ r,
-    double* __restrict__ partials, double* __restrict__ partials_b, int wpr) {
-    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
-    const Seg g = tiled_segment(int(logical_block()), wave, R, L.nI, L.nJ, wpr);
-    double acc = 0, accb = 0;
-    {
-        const Seg& nb = g;
-        const NbB<TU> bu(nb);
-        const NbB<TE> be(nb);
-        const NbB<TR> br(nb);
-        const int nJ = L.nJ, nz = L.nz;
-        const uint64_t PU = uint64_t(L.plane) * sizeof(TU),
-                       PE = uint64_t(L.plane) * sizeof(TE),
-                       PR = uint64_t(L.plane) * sizeof(TR);
-        // uin == nullptr: the iterate before the update is zero
-        auto un = [&](int kk, uint32_t ou, uint32_t oe) -> TU {
-            TU v = uin ? ldb<TU>(layer(uin, kk, PU), ou) : TU(0);
-            if constexpr (HAS_E) v += TU(ldb<TE>(layer(e, kk, PE), oe));
-            return v;
-        };
-        TU um = 0, uc = un(0, bu.c, be.c);
-#pragma unroll
-        for (int k = 0; k < NZ; ++k) {
-            const int kk = clampk(k, nz), kp = clampk(k + 1, nz);
-            const TU up = un(kp, bu.c, be.c);
-            const TU h =
-                ldb<TU>(layer(L.M, kk, PU), bu.c) * uc +
-                hdiff(tab(L.Tlam, kk * nJ + nb.J), tab(L.Tth, kk * (nJ + 1) + nb.J),
-                      tab(L.Tth, kk * (nJ + 1) + nb.J + 1), uc, un(kk, bu.w, be.w),
-                      un(kk, bu.e, be.e), un(kk, bu.s, be.s), un(kk, bu.n, be.n)) +
-                tab(L.Tr, kk * nJ + nb.J) * (uc - um) + tab(L.Tr, (kk + 1) * nJ + nb.J) * (uc - up);
-            const TU bk = ldb<TU>(layer(bv, kk, PU), bu.c);
-            const TU rv = bk - h;
-            if (k < nz && g.valid) {
-                if constexpr (HAS_E) stb<TU>(layer_w(uout, kk, PU), bu.c, uc);
-                stb<TR>(layer_w(r, kk, PR), br.c, TR(rv));
-                acc += double(rv) * double(rv);
-                accb += double(bk) * double(bk);
-            }
-            um = uc;
-            uc = up;
-            // keep the block's wavefronts within a few layers of each other
-            if (k % kResidualSync == kResidualSync - 1) __syncthreads();
-        }
-    }
-    if (partials_b) block_sum2_to(acc, accb, partials + blockIdx.x, partials_b + blockIdx.x);
-    else block_sum_to(acc, partials + blockIdx.x);
-}
-
-// The same refinement step on levels whose step records cover every layer
-// (nz <= kStepStride), walking ranges of LR layers: block b takes range
+//   per-block partial sums of r^2 in FP64, and of b^2 when partials_b is set;
+// or the operator alone, r = H uin (MODE 1) or r = b - H uin (MODE 2), with no
+// sums. It walks ranges of LR layers: block b takes range
 // b / tiles and the tile of R consecutive rows of one 64-column range
 // b % tiles (one wavefront per row), and each wavefront walks its layers
 // upward with the loads of the next P layers in flight, the layers below and
@@ -186,7 +139,7 @@ __global__ __launch_bounds__(64 * R) void k_residual_update(
 // iterate before the update is zero (the first update of a solve from
 // u = 0), and uin is not read.
 template <typename TU, typename TE, typename TR, bool HAS_E, bool HAS_U, int LR, int P, int R,
-          int S, bool FULLI>
+          int S, bool FULLI, int MODE = 0>
 __global__ __launch_bounds__(64 * R) void k_residual_walk(
     LevelView<TU> L, const TU* __restrict__ bv, const TU* __restrict__ uin,
     const TE* __restrict__ e, TU* __restrict__ uout, TR* __restrict__ r,
@@ -199,7 +152,7 @@ __global__ __launch_bounds__(64 * R) void k_residual_walk(
     const uint32_t PU = uint32_t(L.plane) * sizeof(TU), PE = uint32_t(L.plane) * sizeof(TE),
                    PR = uint32_t(L.plane) * sizeof(TR);
     const rsrc_t ru = make_rsrc(HAS_U ? uin : bv, PU * uint32_t(nz)),
-                 rb = make_rsrc(bv, PU * uint32_t(nz)),
+                 rb = make_rsrc(MODE == 1 ? uin : bv, PU * uint32_t(nz)),
                  rm = make_rsrc(L.M, PU * uint32_t(nz)),
                  re = make_rsrc(HAS_E ? (const void*)e : (const void*)uin, PE * uint32_t(nz)),
                  rw = make_rsrc(HAS_E ? (const void*)uout : (const void*)uin, PU * uint32_t(nz)),
@@ -211,7 +164,7 @@ __global__ __launch_bounds__(64 * R) void k_residual_walk(
     const uint32_t ec = g.c * sizeof(TE), es = g.s * sizeof(TE), en = g.n * sizeof(TE),
                    ew = (FULLI ? gcol : g.w) * sizeof(TE), ee = g.e * sizeof(TE);
     const uint32_t rc = g.c * sizeof(TR);
-    const StepCoef<TU>* qp = L.sc + size_t(g.J) * kStepStride;
+    const StepCoef<TU>* qp = L.sc + size_t(g.J) * size_t(L.scs);
 
     // H is applied to a nonzero iterate (else r = b)
     constexpr bool HOP = HAS_U || HAS_E;
@@ -251,7 +204,8 @@ __global__ __launch_bounds__(64 * R) void k_residual_walk(
                 if constexpr (!FULLI) Q.ee = bld<TE>(re, ee, se);
             }
             // b and the mass are read at the cell only: non-temporal loads
-            Q.b = bld<TU, true>(rb, uc, su);
+            if constexpr (MODE != 1) Q.b = bld<TU, true>(rb, uc, su);
+            else Q.b = TU(0);
             if constexpr (HOP) {
                 Q.m = bld<TU, true>(rm, uc, su);
                 Q.q = step_rec(qp, size_t(k));
@@ -303,20 +257,25 @@ __global__ __launch_bounds__(64 * R) void k_residual_walk(
                   q.tc * (xc - xp);
             tb = q.tc;
         }
+        if constexpr (MODE == 1) rv = -rv;   // H u (b is 0)
         // computed here, not sunk (with its loads) into the guarded stores
         asm volatile("" : "+v"(rv));
         const int k = kb + t;
         if (k < nz && g.valid) {
             if constexpr (HAS_E) bst(xc, rw, uc, uint32_t(k) * PU);
             bst(TR(rv), rr, rc, uint32_t(k) * PR);
-            acc += double(rv) * double(rv);
-            accb += double(c.b) * double(c.b);
+            if constexpr (MODE == 0) {
+                acc += double(rv) * double(rv);
+                accb += double(c.b) * double(c.b);
+            }
         }
         um = xc;
         if (t % S == S - 1) __syncthreads();
     }
-    if (partials_b) block_sum2_to(acc, accb, partials + blockIdx.x, partials_b + blockIdx.x);
-    else block_sum_to(acc, partials + blockIdx.x);
+    if constexpr (MODE == 0) {
+        if (partials_b) block_sum2_to(acc, accb, partials + blockIdx.x, partials_b + blockIdx.x);
+        else block_sum_to(acc, partials + blockIdx.x);
+    }
 }
 
 // Block c sums the c-th array of partials (arrays `stride` apart) into out[c].
@@ -445,6 +404,30 @@ __global__ __launch_bounds__(kBlock) void k_fill(T* __restrict__ out, T v, long 
 
 template <typename T>
 void apply(const LevelView<T>& L, const T* x, const T* f, T* y, hipStream_t s) {
+    if constexpr (std::is_same<T, double>::value) {
+        if (L.plane >= kApplyWalkColumns) {
+            const int wpr = segments_per_row(L.nI);
+            const int tiles = tiled_blocks(L.nJ, wpr, kApplyRows);
+            auto go = [&](auto fullc, auto modec) {
+                constexpr int MODE = decltype(modec)::value;
+                k_residual_walk<double, double, double, false, true, kApplyRange,
+                                kResidualAhead, kApplyRows, kResidualSync,
+                                decltype(fullc)::value, MODE>
+                    <<<tiles * ((L.nz + kApplyRange - 1) / kApplyRange), 64 * kApplyRows, 0,
+                       s>>>(L, f, x, nullptr, nullptr, y, nullptr, nullptr, wpr, tiles);
+            };
+            using One = std::integral_constant<int, 1>;
+            using Two = std::integral_constant<int, 2>;
+            if (L.nI % 64 == 0) {
+                if (f) go(std::true_type{}, Two{});
+                else go(std::true_type{}, One{});
+            } else {
+                if (f) go(std::false_type{}, Two{});
+                else go(std::false_type{}, One{});
+            }
+            return;
+        }
+    }
     const dim3 grid(unsigned((L.nI + 63) / 64), unsigned((L.nJ + kApplyRows - 1) / kApplyRows),
                     unsigned((L.nz + apply_layers<T>() - 1) / apply_layers<T>()));
     if (f) k_apply<T, true><<<grid, dim3(64, kApplyRows), 0, s>>>(L, x, f, y);
@@ -457,60 +440,48 @@ int residual_update(const LevelView<TU>& L, const TU* b, const TU* uin, const TE
     const int wpr = segments_per_row(L.nI);
     const int nb = residual_update_blocks(L);
     const bool tall = residual_tile_rows(L.nI, L.nJ) == kResidualTallRows;
-    if (L.nz <= kStepStride) {
-        const int tiles = tiled_blocks(L.nJ, wpr, tall ? kResidualTallRows : 4);
-        const bool full = L.nI % 64 == 0;
-        auto go = [&](auto lrc, auto rc, auto fullc) {
-            constexpr int LR = decltype(lrc)::value, R = decltype(rc)::value;
-            constexpr bool FULLI = decltype(fullc)::value;
-            constexpr int P = kResidualAhead, S = kResidualSync;
-            if (e && uin)
-                k_residual_walk<TU, TE, TR, true, true, LR, P, R, S, FULLI>
-                    <<<nb, 64 * R, 0, s>>>(L, b, uin, e, uout, r, partials, partials_b, wpr, tiles);
-            else if (e)
-                k_residual_walk<TU, TE, TR, true, false, LR, P, R, S, FULLI>
-                    <<<nb, 64 * R, 0, s>>>(L, b, uin, e, uout, r, partials, partials_b, wpr, tiles);
-            else if (uin)
-                k_residual_walk<TU, TE, TR, false, true, LR, P, R, S, FULLI>
-                    <<<nb, 64 * R, 0, s>>>(L, b, uin, e, uout, r, partials, partials_b, wpr, tiles);
-            else   // r = b: no neighbours (the same blocks and sums as with u = 0)
-                k_residual_walk<TU, TE, TR, false, false, LR, P, R, S, false>
-                    <<<nb, 64 * R, 0, s>>>(L, b, uin, e, uout, r, partials, partials_b, wpr, tiles);
-        };
-        auto by_rows = [&](auto lrc, auto fullc) {
-            if (tall) go(lrc, std::integral_constant<int, kResidualTallRows>{}, fullc);
-            else go(lrc, std::integral_constant<int, 4>{}, fullc);
-        };
-        auto by_full = [&](auto lrc) {
-            if (full) by_rows(lrc, std::true_type{});
-            else by_rows(lrc, std::false_type{});
-        };
-        if (residual_walk_range(L.nI, L.nJ, L.nz) == kResidualShortRange)
-            by_full(std::integral_constant<int, kResidualShortRange>{});
-        else
-            by_full(std::integral_constant<int, kResidualRange>{});
-        return nb;
-    }
-    with_nz(L.nz, [&](auto nzc) {
-        constexpr int NZ = decltype(nzc)::value;
-#define MG_RESIDUAL_LAUNCH(HE, R) \
-    k_residual_update<TU, TE, TR, NZ, HE, R><<<nb, 64 * R, 0, s>>>(L, b, uin, e, uout, r, partials, \
-                                                                  partials_b, wpr)
-        if (tall) {
-            if (e) MG_RESIDUAL_LAUNCH(true, kResidualTallRows);
-            else MG_RESIDUAL_LAUNCH(false, kResidualTallRows);
-        } else {
-            if (e) MG_RESIDUAL_LAUNCH(true, 4); else MG_RESIDUAL_LAUNCH(false, 4);
-        }
-#undef MG_RESIDUAL_LAUNCH
-    });
+    const int tiles = tiled_blocks(L.nJ, wpr, tall ? kResidualTallRows : 4);
+    const bool full = L.nI % 64 == 0;
+    auto go = [&](auto lrc, auto rc, auto fullc) {
+        constexpr int LR = decltype(lrc)::value, R = decltype(rc)::value;
+        constexpr bool FULLI = decltype(fullc)::value;
+        constexpr int P = kResidualAhead, S = kResidualSync;
+        if (e && uin)
+            k_residual_walk<TU, TE, TR, true, true, LR, P, R, S, FULLI>
+                <<<nb, 64 * R, 0, s>>>(L, b, uin, e, uout, r, partials, partials_b, wpr, tiles);
+        else if (e)
+            k_residual_walk<TU, TE, TR, true, false, LR, P, R, S, FULLI>
+                <<<nb, 64 * R, 0, s>>>(L, b, uin, e, uout, r, partials, partials_b, wpr, tiles);
+        else if (uin)
+            k_residual_walk<TU, TE, TR, false, true, LR, P, R, S, FULLI>
+                <<<nb, 64 * R, 0, s>>>(L, b, uin, e, uout, r, partials, partials_b, wpr, tiles);
+        else   // r = b: no neighbours (the same blocks and sums as with u = 0)
+            k_residual_walk<TU, TE, TR, false, false, LR, P, R, S, false>
+                <<<nb, 64 * R, 0, s>>>(L, b, uin, e, uout, r, partials, partials_b, wpr, tiles);
+    };
+    auto by_rows = [&](auto lrc, auto fullc) {
+        if (tall) go(lrc, std::integral_constant<int, kResidualTallRows>{}, fullc);
+        else go(lrc, std::integral_constant<int, 4>{}, fullc);
+    };
+    auto by_full = [&](auto lrc) {
+        if (full) by_rows(lrc, std::true_type{});
+        else by_rows(lrc, std::false_type{});
+    };
+    if (residual_walk_range(L.nI, L.nJ, L.nz) == kResidualShortRange)
+        by_full(std::integral_constant<int, kResidualShortRange>{});
+    else
+        by_full(std::integral_constant<int, kResidualRange>{});
     return nb;
 }
 
 template <typename TU>
+int residual_tiles(const LevelView<TU>& L) {
+    return tiled_blocks(L.nJ, segments_per_row(L.nI), residual_tile_rows(L.nI, L.nJ));
+}
+
+template <typename TU>
 int residual_update_blocks(const LevelView<TU>& L) {
-    const int tiles = tiled_blocks(L.nJ, segments_per_row(L.nI), residual_tile_rows(L.nI, L.nJ));
-    if (L.nz > kStepStride) return tiles;
+    const int tiles = residual_tiles(L);
     const int lr = residual_walk_range(L.nI, L.nJ, L.nz);
     return tiles * ((L.nz + lr - 1) / lr);
 }
@@ -554,10 +525,6 @@ void fill(T* out, T v, long long n, hipStream_t s) {
     k_fill<T><<<grid_stride_blocks(n), kBlock, 0, s>>>(out, v, n);
 }
 
-template void apply<float>(const LevelView<float>&, const float*, const float*, float*,
-                           hipStream_t);
-template void apply<double>(const LevelView<double>&, const double*, const double*, double*,
-                            hipStream_t);
 template int residual_update<double, float, float>(const LevelView<double>&, const double*,
                                                   const double*, const float*, double*,
                                                   float*, double*, double*, hipStream_t);
@@ -568,6 +535,11 @@ template int residual_update<double, double, double>(const LevelView<double>&,
 template int residual_update<float, float, float>(const LevelView<float>&, const float*,
                                                  const float*, const float*, float*, float*,
                                                  double*, double*, hipStream_t);
+template void apply<float>(const LevelView<float>&, const float*, const float*, float*,
+                           hipStream_t);
+template void apply<double>(const LevelView<double>&, const double*, const double*, double*,
+                            hipStream_t);
+template int residual_tiles<double>(const LevelView<double>&);
 template int residual_update_blocks<double>(const LevelView<double>&);
 template int residual_update_blocks<float>(const LevelView<float>&);
 template void cast<double, float>(const double*, float*, long long, hipStream_t);

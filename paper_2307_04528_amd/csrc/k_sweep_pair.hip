@@ -203,7 +203,7 @@ void k_sweep_pair(LevelView<float> L, const float* __restrict__ f, const float* 
         }
         if constexpr (PART == 1)
             q = *reinterpret_cast<const f4*>(
-                &L.sc[(size_t(top) * size_t(nJ) + size_t(r)) * kStepStride + lane]);
+                &L.sc[(size_t(top) * size_t(nJ) + size_t(r)) * size_t(L.scs) + lane]);
     };
     using Part0 = std::integral_constant<int, 0>;
     using Part1 = std::integral_constant<int, 1>;

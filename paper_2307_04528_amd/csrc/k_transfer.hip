@@ -113,9 +113,8 @@ __global__ __launch_bounds__(kBlock) void k_restrict_seg(LevelView<T> F, Transfe
         if (k0 + d < nz && gc.valid) stb<T>(layer_w(fc, k0 + d, Pcb), oc, out[d]);
 }
 
-// fc = R (f - H x) on the larger levels (see RestrictWalk), whose step
-// records cover every layer (nz <= kStepStride). One wavefront per (row-aligned coarse
-// segment, range of LR layers), range-major, walks its layers upward with
+// fc = R (f - H x) on the larger levels (see RestrictWalk). One wavefront per
+// (row-aligned coarse segment, range of LR layers), range-major, walks its layers upward with
 // the loads of the next P layers in flight. The children of a layer serve
 // as the layer above of the step before and the layer below of the step
 // after, so each is loaded once (and one layer below the range). A lane
@@ -180,8 +179,8 @@ void k_restrict_walk(LevelView<T> F, TransferView<T> X, const T* __restrict__ f,
     const uint32_t Pb = uint32_t(F.plane) * S, Pcb = uint32_t(X.nIc) * uint32_t(X.nJc) * S;
     const rsrc_t rx = make_rsrc(x, Pb * uint32_t(nz)), rf = make_rsrc(f, Pb * uint32_t(nz)),
                  rm = make_rsrc(F.M, Pb * uint32_t(nz)), ro = make_rsrc(fc, Pcb * uint32_t(nz));
-    const StepCoef<T>* q0p = F.sc + size_t(j0) * kStepStride;
-    const StepCoef<T>* q1p = F.sc + size_t(j1) * kStepStride;
+    const StepCoef<T>* q0p = F.sc + size_t(j0) * size_t(F.scs);
+    const StepCoef<T>* q1p = F.sc + size_t(j1) * size_t(F.scs);
     const uint32_t oc = gc.c * S;
     const int kb = rg * LR;
 
@@ -437,7 +436,7 @@ void restrict_residual(const LevelView<T>& F, const TransferView<T>& X, const T*
     constexpr int waves = kBlock / 64;
     constexpr int DLS = kRestrictLayers;
     constexpr int DLL = std::is_same<T, float>::value ? kRestrictLayersLarge32 : DLS;
-    if (x && F.plane >= RestrictWalk<T>::MinColumns && F.nz <= kStepStride) {
+    if (x && F.plane >= RestrictWalk<T>::MinColumns) {
         using C = RestrictWalk<T>;
         const int units = nsegc * ((F.nz + C::LR - 1) / C::LR);
         const int nb = (units + waves - 1) / waves;

@@ -12,12 +12,13 @@ namespace mgk {
 // k = dir ? nz-1-t : t (clamped to [0, nz-1]): Tlam[k][J], Tth[k][J],
 // Tth[k][J+1], and tc, the vertical coupling to the next layer in that
 // direction (Tr[k+1][J] upward, Tr[k][J] downward). Table layout
-// [dir][J][t], kStepStride records per row.
+// [dir][J][t], step_stride(nz) records per row: as many as the layers, and
+// as the padded steps of the compiled sweeps reach.
 template <typename T>
 struct alignas(4 * sizeof(T)) StepCoef {
     T tl, ts, tn, tc;
 };
-constexpr int kStepStride = 72;
+inline int step_stride(int nz) { return nz <= 72 ? 72 : 136; }
 
 // Geometry and operator data of one level, in the precision T of the kernels
 // that read it. Fields are [k][J][i] with i fastest; plane = nI*nJ.
@@ -30,7 +31,8 @@ struct LevelView {
     const T* Tr;     // [nz+1][nJ], face F below layer F
     const T* M;      // [nz][plane] mass sum(alpha V)
     const T* invp;   // [nz][plane] inverse pivots of the twisted factorisation of H_z
-    const StepCoef<T>* sc;   // [2][nJ][kStepStride] step records (see StepCoef)
+    const StepCoef<T>* sc;   // [2][nJ][scs] step records (see StepCoef)
+    int scs;
 };
 
 // Maps between a fine level and the next coarser one.
@@ -154,6 +156,9 @@ int residual_update(const LevelView<TU>& L, const TU* b, const TU* uin, const TE
 // Blocks (hence partial sums) residual_update launches for level L.
 template <typename TU>
 int residual_update_blocks(const LevelView<TU>& L);
+// Row tiles of it (blocks per range of layers).
+template <typename TU>
+int residual_tiles(const LevelView<TU>& L);
 
 // out[c] = sum of partials[c*stride + 0..n) in a fixed order, c < count.
 void sum_partials(const double* partials, int n, double* out, hipStream_t s, int count = 1,

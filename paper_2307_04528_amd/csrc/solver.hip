@@ -107,6 +107,7 @@ struct mg_handle {
     double* host_scalar = nullptr; // pinned host copy [2]
     hipEvent_t scalar_ready = nullptr;   // recorded after the copy to host_scalar
     int max_partials = 0;
+    int grid_partials = 0;         // the same with one range of layers per column
     size_t max_lds = 64 * 1024;    // LDS bytes a block may use (device limit)
     int device = 0;                // the GPU the handle lives on
     bool no_events = false;        // record no HIP events (mg_solve_noalloc)
@@ -192,12 +193,13 @@ mg_status dalloc(mg_handle* h, T** p, size_t count) {
 template <typename T>
 std::vector<mgk::StepCoef<T>> step_table(const mgs::Level& s) {
     const int nJ = s.nJ, nz = s.nz;
-    std::vector<mgk::StepCoef<T>> tab(size_t(2) * nJ * mgk::kStepStride);
+    const int stride = mgk::step_stride(nz);
+    std::vector<mgk::StepCoef<T>> tab(size_t(2) * nJ * stride);
     for (int dir = 0; dir < 2; ++dir)
         for (int J = 0; J < nJ; ++J)
-            for (int t = 0; t < mgk::kStepStride; ++t) {
+            for (int t = 0; t < stride; ++t) {
                 const int k = std::min(std::max(dir ? nz - 1 - t : t, 0), nz - 1);
-                mgk::StepCoef<T>& q = tab[(size_t(dir) * nJ + J) * mgk::kStepStride + t];
+                mgk::StepCoef<T>& q = tab[(size_t(dir) * nJ + J) * stride + t];
                 q.tl = T(s.Tlam[size_t(k) * nJ + J]);
                 q.ts = T(s.Tth[size_t(k) * (nJ + 1) + J]);
                 q.tn = T(s.Tth[size_t(k) * (nJ + 1) + J + 1]);
@@ -222,11 +224,13 @@ mgk::LevelView<T> view(const DevLevel& d);
 
 template <>
 mgk::LevelView<float> view<float>(const DevLevel& d) {
-    return {d.nI, d.nJ, d.nz, d.plane, d.Tlam32, d.Tth32, d.Tr32, d.M32, d.invp32, d.sc32};
+    return {d.nI, d.nJ, d.nz, d.plane, d.Tlam32, d.Tth32, d.Tr32, d.M32, d.invp32, d.sc32,
+            mgk::step_stride(d.nz)};
 }
 template <>
 mgk::LevelView<double> view<double>(const DevLevel& d) {
-    return {d.nI, d.nJ, d.nz, d.plane, d.Tlam64, d.Tth64, d.Tr64, d.M64, d.invp64, d.sc64};
+    return {d.nI, d.nJ, d.nz, d.plane, d.Tlam64, d.Tth64, d.Tr64, d.M64, d.invp64, d.sc64,
+            mgk::step_stride(d.nz)};
 }
 
 template <typename T>
@@ -1040,6 +1044,9 @@ mg_status build(mg_handle* h, const double* alpha) {
     DevLevel& f = h->lv[0];
     h->max_partials = std::max({mgk::residual_update_blocks(view<double>(f)),
                                 mgk::blocks_for(f.plane), 8192});
+    h->grid_partials = std::max({f.nz <= 72 ? mgk::residual_update_blocks(view<double>(f))
+                                            : mgk::residual_tiles(view<double>(f)),
+                                 mgk::blocks_for(f.plane), 8192});
     MG_TRY(dalloc(h, &h->partials, 2 * size_t(h->max_partials)));
     MG_TRY(dalloc(h, &h->scalar, 2));
     MG_TRY(dalloc(h, &h->u_alt, f.n));
@@ -1160,7 +1167,10 @@ mg_status one_vcycle(mg_handle* h, const double* f, double* x, bool transposed) 
 // library's own. Each GPU holds one copy (until the process ends); its
 // address there is looked up once, at the first mg_setup on that GPU, with
 // that GPU current. Host code uses that address, never the array's name.
-constexpr size_t kScratchDoubles = 65536 + 256;
+constexpr size_t kScratchDoubles = 131072 + 256;
+// Grids that need more partials than this with one range of layers per column
+// are refused.
+constexpr size_t kScratchGrid = (65536 + 256 - 2) / 2;
 __device__ __align__(256) double scratch[kScratchDoubles];
 constexpr int kMaxDevices = 64;
 double* g_scratch[kMaxDevices] = {};
@@ -1369,7 +1379,7 @@ mg_status mg_solve_noalloc(mg_handle* h, const double* rhs, double* u, double to
     double* sp = (h->device >= 0 && h->device < kMaxDevices) ? g_scratch[h->device] : nullptr;
     if (!sp) return fail(h, MG_ERR_ARG, "no scratch address for device %d", h->device);
     const size_t need = 2 * size_t(h->max_partials) + 2;
-    if (need > kScratchDoubles)
+    if (size_t(h->grid_partials) > kScratchGrid || need > kScratchDoubles)
         return fail(h, MG_ERR_ARG,
                     "grid too large for mg_solve_noalloc: %zu scratch values needed, %zu "
                     "available", need, kScratchDoubles);

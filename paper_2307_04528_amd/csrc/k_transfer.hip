@@ -28,9 +28,10 @@ __device__ __forceinline__ pair_t<T> ld2(gcptr base, uint32_t boff) {
 // of the chunk's layers and the layers just outside it are loaded once.
 // Chunk depth: 7 layers for FP32 on large levels (7 divides the 70-layer
 // workloads: 185 us per finest-level launch on 1024x768x70, against 199 us
-// with 4 layers, 190 with 6 and 212 with 8); 4 elsewhere (smaller levels
-// need the parallelism of more chunks, and FP64 solves were 5 % slower with 7).
-constexpr int kRestrictLayers = 4;
+// with 4 layers, 190 with 6 and 212 with 8); 2 elsewhere (small levels need
+// the parallelism of more chunks: 3.9 us on 18x26x38 against 4.8 with 4 and 3.7
+// with 1, 9.8 on 192x144x70 against 11.1 and 10.4).
+constexpr int kRestrictLayers = 2;
 constexpr int kRestrictLayersLarge32 = 7;
 template <typename T, bool HAS_X, int DL>
 __global__ __launch_bounds__(kBlock) void k_restrict_seg(LevelView<T> F, TransferView<T> X,

@@ -32,7 +32,8 @@ constexpr int kResidualTallRows = 16;
 // tiles take 2.78-2.90 ms against 2.99-3.07 ms (FP64: 3.54-3.59 against
 // 3.82-3.83 ms).
 constexpr int kResidualRange = 70;
-constexpr int kResidualShortRange = 16;
+constexpr int kResidualShortRange = 8;
+constexpr int kResidualTinyRange = 4;
 constexpr int kResidualAhead = 3;
 
 static int residual_tile_rows(int nI, int nJ) {
@@ -44,12 +45,18 @@ static int residual_tile_rows(int nI, int nJ) {
 
 // Layers per walk: whole columns on levels with enough tall tiles to fill
 // the GPU; ranges of kResidualShortRange layers on smaller levels, whose
-// whole-column walks leave a few wavefronts per CU (384x192x70: 1152
-// wavefronts, 54 us; in ranges of 16 layers five times as many, 45 us).
+// whole-column walks leave a few wavefronts per CU (384x192x70: 54 us with
+// whole columns, 47.3 with ranges of 16 layers, 45.4 with 8 and with 4;
+// 288x192x38 25.5, 22.8 and 23.4); of kResidualTinyRange on levels that give
+// fewer than one block per CU otherwise (FP64 on 64x32x16: 8.4 us with 16
+// layers, 6.2 with 8, 4.9 with 4).
 static int residual_walk_range(int nI, int nJ, int nz) {
-    if (nz <= kResidualShortRange) return kResidualShortRange;
-    return residual_tile_rows(nI, nJ) == kResidualTallRows ? kResidualRange
-                                                           : kResidualShortRange;
+    if (residual_tile_rows(nI, nJ) == kResidualTallRows)
+        return nz <= 16 ? 16 : kResidualRange;
+    return (long long)dev::tiled_blocks(nJ, dev::segments_per_row(nI), 4) *
+                       ((nz + kResidualShortRange - 1) / kResidualShortRange) < 256
+               ? kResidualTinyRange
+               : kResidualShortRange;
 }
 
 namespace {
@@ -122,6 +129,52 @@ __global__ __launch_bounds__(64 * kApplyRows) void k_apply(LevelView<T> L,
         if (k0 + d < nz) y[size_t(k0 + d) * P + c] = hs[d];
 }
 
+// The block's partial sums (in `mine`, written by thread 0) and the sums over
+// all blocks, by the block that finishes last: in the fixed order of the
+// partials whichever block it is, written to norms[0] (and norms[1] with
+// partials_b), which is host memory. That saves two launches per refinement
+// step, the reduction and the copy of its result: 9 us of the 92 us of an
+// iteration on 64x32x16.
+// The partials are stored and read with agent scope, past the XCDs' own
+// caches, and a block counts itself done only after its stores have been
+// acknowledged; the last block sets the count back to zero for the next step.
+__device__ __forceinline__ void sum_by_last_block(const double* mine, double* partials,
+                                                  double* partials_b, unsigned* done,
+                                                  double* norms) {
+    __shared__ unsigned last;
+    if (threadIdx.x == 0) {
+        __hip_atomic_store(partials + blockIdx.x, mine[0], __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+        if (partials_b)
+            __hip_atomic_store(partials_b + blockIdx.x, mine[1], __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        const unsigned n = __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED,
+                                                  __HIP_MEMORY_SCOPE_AGENT);
+        last = n + 1 == gridDim.x ? 1u : 0u;
+    }
+    __syncthreads();
+    if (last == 0) return;   // block-uniform
+    __shared__ double red[1024];
+    for (int c = 0; c < (partials_b ? 2 : 1); ++c) {
+        const double* p = c ? partials_b : partials;
+        double a = 0;
+        for (unsigned t = threadIdx.x; t < gridDim.x; t += blockDim.x)
+            a += __hip_atomic_load(p + t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        red[threadIdx.x] = a;
+        __syncthreads();
+        for (unsigned w = blockDim.x / 2; w > 0; w >>= 1) {
+            if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+            __syncthreads();
+        }
+        if (threadIdx.x == 0)
+            __hip_atomic_store(norms + c, red[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __syncthreads();
+    }
+    if (threadIdx.x == 0)
+        __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Refinement step on the finest level (MODE 0), in the precision TU of the
 // iterate (FP64; FP32 in the pure single-precision solve):
 //   unew = uin + e (HAS_E; written to uout), r = b - H unew (stored as TR),
@@ -143,7 +196,8 @@ template <typename TU, typename TE, typename TR, bool HAS_E, bool HAS_U, int LR,
 __global__ __launch_bounds__(64 * R) void k_residual_walk(
     LevelView<TU> L, const TU* __restrict__ bv, const TU* __restrict__ uin,
     const TE* __restrict__ e, TU* __restrict__ uout, TR* __restrict__ r,
-    double* __restrict__ partials, double* __restrict__ partials_b, int wpr, int tiles) {
+    double* partials, double* partials_b, int wpr, int tiles, unsigned* done,
+    double* norms) {
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
     const int blk = int(logical_block());
     const int rg = blk / tiles;
@@ -273,8 +327,10 @@ __global__ __launch_bounds__(64 * R) void k_residual_walk(
         if (t % S == S - 1) __syncthreads();
     }
     if constexpr (MODE == 0) {
-        if (partials_b) block_sum2_to(acc, accb, partials + blockIdx.x, partials_b + blockIdx.x);
-        else block_sum_to(acc, partials + blockIdx.x);
+        __shared__ double mine[2];
+        if (partials_b) block_sum2_to(acc, accb, &mine[0], &mine[1]);
+        else block_sum_to(acc, &mine[0]);
+        sum_by_last_block(mine, partials, partials_b, done, norms);
     }
 }
 
@@ -327,38 +383,69 @@ __global__ __launch_bounds__(kBlock) void k_fine_mass(LevelView<double> L,
 //                            + Tr_{m+1} h_{m+1} / (Tr_{m+1} + h_{m+1}))
 // These are the textbook pivots D_k - Tr^2 / p of each elimination without
 // the cancellation (every g, h >= mt > 0).
-__global__ __launch_bounds__(kBlock) void k_pivots(LevelView<double> L,
-                                                   double* __restrict__ invp64,
-                                                   float* __restrict__ invp32,
-                                                   float* __restrict__ M32) {
-    const uint32_t col = global_index();
-    if (col >= uint32_t(L.plane)) return;
+// The recurrences are serial chains of divisions, which bound the smaller
+// levels: a column's two halves are two lanes' work (wavefronts 0 and 1 of a
+// block of 64 columns), each step has one division (the quotient Tr g / (Tr + g)
+// of a layer takes the stored inverse of the layer before), and the masses of
+// the next layers are loaded ahead. 9 us per level against 37 with one lane
+// per column and two divisions per layer.
+__global__ __launch_bounds__(128) void k_pivots(LevelView<double> L,
+                                                double* __restrict__ invp64,
+                                                float* __restrict__ invp32,
+                                                float* __restrict__ M32) {
+    const bool top = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)) != 0;
+    const int lane = int(threadIdx.x & 63u);
+    const uint32_t P = uint32_t(L.plane);
+    const uint32_t want = logical_block() * 64u + uint32_t(lane);
+    const bool valid = want < P;
+    const uint32_t col = valid ? want : P - 1;
     const int J = int(col / uint32_t(L.nI)), nJ = L.nJ, nz = L.nz, m = nz / 2;
-    auto off = [&](int k) { return size_t(k) * size_t(L.plane) + col; };
-    auto mt = [&](int k) {
-        return L.M[off(k)] + 2.0 * L.Tlam[k * nJ + J] + L.Tth[k * (nJ + 1) + J] +
+    auto off = [&](int k) { return size_t(k) * size_t(P) + col; };
+    auto mt = [&](int k, double M) {
+        return M + 2.0 * L.Tlam[k * nJ + J] + L.Tth[k * (nJ + 1) + J] +
                L.Tth[k * (nJ + 1) + J + 1];
     };
-    auto tr = [&](int F) { return L.Tr[F * nJ + J]; };
-    auto put = [&](int k, double ip) {
+    auto put = [&](int k, double M, double ip) {
+        if (!valid) return;
         invp64[off(k)] = ip;
         invp32[off(k)] = float(ip);
-        M32[off(k)] = float(L.M[off(k)]);
+        M32[off(k)] = float(M);
     };
-    double g = 0;
-    for (int k = 0; k < m; ++k) {
-        g = (k == 0) ? mt(0) : mt(k) + tr(k) * g / (tr(k) + g);
-        put(k, 1.0 / (tr(k + 1) + g));
+    // step t: layer t from the bottom, nz-1-t from the top, m excluded
+    const int steps = top ? nz - 1 - m : m;
+    const int k0 = top ? nz - 1 : 0, ks = top ? -1 : 1;
+    constexpr int D = 4;
+    double Mn[D], q = 0;   // q: Tr g / (Tr + g) of the layer before
+#pragma unroll
+    for (int d = 0; d < D; ++d) Mn[d] = L.M[off(k0 + (d < steps ? d : 0) * ks)];
+    for (int t0 = 0; t0 < steps; t0 += D) {
+        double Mc[D];
+#pragma unroll
+        for (int d = 0; d < D; ++d) Mc[d] = Mn[d];
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            const int t = t0 + D + d;
+            Mn[d] = L.M[off(k0 + (t < steps ? t : 0) * ks)];
+        }
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            const int t = t0 + d;
+            if (t >= steps) break;   // wave-uniform
+            const int k = k0 + t * ks;
+            const double g = mt(k, Mc[d]) + q;
+            const double tr = L.Tr[(top ? k : k + 1) * nJ + J];
+            const double ip = 1.0 / (tr + g);
+            put(k, Mc[d], ip);
+            q = tr * g * ip;
+        }
     }
-    double h = 0;
-    for (int k = nz - 1; k > m; --k) {
-        h = (k == nz - 1) ? mt(k) : mt(k) + tr(k + 1) * h / (tr(k + 1) + h);
-        put(k, 1.0 / (tr(k) + h));
+    __shared__ double qt[64];
+    if (top) qt[lane] = q;
+    __syncthreads();
+    if (!top) {
+        const double M = L.M[off(m)];
+        put(m, M, 1.0 / (mt(m, M) + q + qt[lane]));
     }
-    double d = mt(m);
-    if (m > 0) d += tr(m) * g / (tr(m) + g);
-    if (m < nz - 1) d += tr(m + 1) * h / (tr(m + 1) + h);
-    put(m, 1.0 / d);
 }
 
 __global__ __launch_bounds__(kBlock) void k_grad_alpha(LevelView<double> L,
@@ -414,7 +501,8 @@ void apply(const LevelView<T>& L, const T* x, const T* f, T* y, hipStream_t s) {
                                 kResidualAhead, kApplyRows, kResidualSync,
                                 decltype(fullc)::value, MODE>
                     <<<tiles * ((L.nz + kApplyRange - 1) / kApplyRange), 64 * kApplyRows, 0,
-                       s>>>(L, f, x, nullptr, nullptr, y, nullptr, nullptr, wpr, tiles);
+                       s>>>(L, f, x, nullptr, nullptr, y, nullptr, nullptr, wpr, tiles, nullptr,
+                       nullptr);
             };
             using One = std::integral_constant<int, 1>;
             using Two = std::integral_constant<int, 2>;
@@ -436,7 +524,8 @@ void apply(const LevelView<T>& L, const T* x, const T* f, T* y, hipStream_t s) {
 
 template <typename TU, typename TE, typename TR>
 int residual_update(const LevelView<TU>& L, const TU* b, const TU* uin, const TE* e, TU* uout,
-                    TR* r, double* partials, double* partials_b, hipStream_t s) {
+                    TR* r, double* partials, double* partials_b, unsigned* done, double* norms,
+                    hipStream_t s) {
     const int wpr = segments_per_row(L.nI);
     const int nb = residual_update_blocks(L);
     const bool tall = residual_tile_rows(L.nI, L.nJ) == kResidualTallRows;
@@ -448,29 +537,35 @@ int residual_update(const LevelView<TU>& L, const TU* b, const TU* uin, const TE
         constexpr int P = kResidualAhead, S = kResidualSync;
         if (e && uin)
             k_residual_walk<TU, TE, TR, true, true, LR, P, R, S, FULLI>
-                <<<nb, 64 * R, 0, s>>>(L, b, uin, e, uout, r, partials, partials_b, wpr, tiles);
+                <<<nb, 64 * R, 0, s>>>(L, b, uin, e, uout, r, partials, partials_b, wpr, tiles,
+                                        done, norms);
         else if (e)
             k_residual_walk<TU, TE, TR, true, false, LR, P, R, S, FULLI>
-                <<<nb, 64 * R, 0, s>>>(L, b, uin, e, uout, r, partials, partials_b, wpr, tiles);
+                <<<nb, 64 * R, 0, s>>>(L, b, uin, e, uout, r, partials, partials_b, wpr, tiles,
+                                        done, norms);
         else if (uin)
             k_residual_walk<TU, TE, TR, false, true, LR, P, R, S, FULLI>
-                <<<nb, 64 * R, 0, s>>>(L, b, uin, e, uout, r, partials, partials_b, wpr, tiles);
+                <<<nb, 64 * R, 0, s>>>(L, b, uin, e, uout, r, partials, partials_b, wpr, tiles,
+                                        done, norms);
         else   // r = b: no neighbours (the same blocks and sums as with u = 0)
             k_residual_walk<TU, TE, TR, false, false, LR, P, R, S, false>
-                <<<nb, 64 * R, 0, s>>>(L, b, uin, e, uout, r, partials, partials_b, wpr, tiles);
+                <<<nb, 64 * R, 0, s>>>(L, b, uin, e, uout, r, partials, partials_b, wpr, tiles,
+                                        done, norms);
     };
-    auto by_rows = [&](auto lrc, auto fullc) {
-        if (tall) go(lrc, std::integral_constant<int, kResidualTallRows>{}, fullc);
-        else go(lrc, std::integral_constant<int, 4>{}, fullc);
+    const int range = residual_walk_range(L.nI, L.nJ, L.nz);
+    auto low = [&](auto lrc) {
+        if (full) go(lrc, std::integral_constant<int, 4>{}, std::true_type{});
+        else go(lrc, std::integral_constant<int, 4>{}, std::false_type{});
     };
-    auto by_full = [&](auto lrc) {
-        if (full) by_rows(lrc, std::true_type{});
-        else by_rows(lrc, std::false_type{});
+    auto high = [&](auto lrc) {
+        constexpr int R = kResidualTallRows;
+        if (full) go(lrc, std::integral_constant<int, R>{}, std::true_type{});
+        else go(lrc, std::integral_constant<int, R>{}, std::false_type{});
     };
-    if (residual_walk_range(L.nI, L.nJ, L.nz) == kResidualShortRange)
-        by_full(std::integral_constant<int, kResidualShortRange>{});
-    else
-        by_full(std::integral_constant<int, kResidualRange>{});
+    if (range == kResidualRange) high(std::integral_constant<int, kResidualRange>{});
+    else if (range == 16) high(std::integral_constant<int, 16>{});
+    else if (range == kResidualShortRange) low(std::integral_constant<int, kResidualShortRange>{});
+    else low(std::integral_constant<int, kResidualTinyRange>{});
     return nb;
 }
 
@@ -501,7 +596,7 @@ int fine_mass(const LevelView<double>& L, const double* V, const double* alpha, 
 
 void pivots(const LevelView<double>& L, double* invp64, float* invp32, float* M32,
             hipStream_t s) {
-    k_pivots<<<blocks_for(L.plane), kBlock, 0, s>>>(L, invp64, invp32, M32);
+    k_pivots<<<int((L.plane + 63) / 64), 128, 0, s>>>(L, invp64, invp32, M32);
 }
 
 void grad_alpha(const LevelView<double>& L, const double* V, const double* lam,
@@ -527,14 +622,17 @@ void fill(T* out, T v, long long n, hipStream_t s) {
 
 template int residual_update<double, float, float>(const LevelView<double>&, const double*,
                                                   const double*, const float*, double*,
-                                                  float*, double*, double*, hipStream_t);
+                                                  float*, double*, double*, unsigned*, double*,
+                                                  hipStream_t);
 template int residual_update<double, double, double>(const LevelView<double>&,
                                                      const double*, const double*,
                                                      const double*, double*, double*,
-                                                     double*, double*, hipStream_t);
+                                                     double*, double*, unsigned*, double*,
+                                                     hipStream_t);
 template int residual_update<float, float, float>(const LevelView<float>&, const float*,
                                                  const float*, const float*, float*, float*,
-                                                 double*, double*, hipStream_t);
+                                                 double*, double*, unsigned*, double*,
+                                                 hipStream_t);
 template void apply<float>(const LevelView<float>&, const float*, const float*, float*,
                            hipStream_t);
 template void apply<double>(const LevelView<double>&, const double*, const double*, double*,

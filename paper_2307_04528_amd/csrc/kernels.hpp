@@ -144,15 +144,17 @@ void inject_add(const LevelView<T>& F, const TransferView<T>& X, const T* xc, T*
 // Refinement step on the finest level, in the iterate's precision TU (FP64;
 // FP32 in the pure single-precision solve):
 //   unew = uin + e (or uin when e == nullptr), written to uout if set;
-//   r = b - H unew, stored as TR; per-block partial sums of r^2 in FP64,
-//   and of b^2 into partials_b when it is not null.
+//   r = b - H unew, stored as TR; the sums of r^2 (and of b^2 when partials_b
+//   is not null) in FP64 into norms[0] (norms[1]), host memory, through
+//   per-block partial sums; *done counts the blocks (0 before and after).
 // uin == nullptr stands for a zero iterate (a solve from u = 0): it is not
 // read, and with e == nullptr as well the step is r = b.
 // Returns the number of blocks (partials written): at most
 // max(residual_update_blocks(L), blocks_for(L.plane)).
 template <typename TU, typename TE, typename TR>
 int residual_update(const LevelView<TU>& L, const TU* b, const TU* uin, const TE* e, TU* uout,
-                    TR* r, double* partials, double* partials_b, hipStream_t s);
+                    TR* r, double* partials, double* partials_b, unsigned* done, double* norms,
+                    hipStream_t s);
 // Blocks (hence partial sums) residual_update launches for level L.
 template <typename TU>
 int residual_update_blocks(const LevelView<TU>& L);

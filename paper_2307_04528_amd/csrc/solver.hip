@@ -3,8 +3,7 @@
 // Outer loop (paper Section 2: each iteration reduces ||b - Hu||): in FP64,
 //   r = b - H u;  while ||r|| > tol ||b||:  e = V(r);  u += e;  r = b - H u
 // with the V-cycle V in FP32 (mixed) or FP64. The update, the residual and its
-// norm are one fused FP64 kernel; the norm is the only per-iteration
-// device-to-host transfer (8 bytes).
+// norm are one fused FP64 kernel, which writes the norm to host memory.
 //
 // V-cycle on level l with right-hand side f (Sections 2, 2.1, 2.3):
 //   x = omega H_z^{-1} f; (nu_pre - 1) more sweeps;
@@ -104,8 +103,9 @@ struct mg_handle {
     float *u32a = nullptr, *u32b = nullptr, *b32 = nullptr;   // MG_PREC_FP32 solve
     double* partials = nullptr;
     double* scalar = nullptr;      // device: reduced values [2]
-    double* host_scalar = nullptr; // pinned host copy [2]
-    hipEvent_t scalar_ready = nullptr;   // recorded after the copy to host_scalar
+    double* host_scalar = nullptr; // pinned host memory: the reduced values [2]
+    hipEvent_t scalar_ready = nullptr;   // recorded after what writes host_scalar
+    unsigned* blocks_done = nullptr;     // blocks of the refinement step that are done
     int max_partials = 0;
     int grid_partials = 0;         // the same with one range of layers per column
     size_t max_lds = 64 * 1024;    // LDS bytes a block may use (device limit)
@@ -743,7 +743,7 @@ mg_status sync_scalar(mg_handle* h, double* out) {
 // FP32 in the pure single-precision solve) and the correction e and
 // residual r in the V-cycle's precision T.
 // Enqueues the step; its ||r||^2 (and ||b||^2 with with_bnorm, summed in the
-// same pass) reaches the host with post_scalar, read by finish_step.
+// same pass) is written to host_scalar by the kernel, read by finish_step.
 template <typename T, typename U>
 mg_status refine_step(mg_handle* h, const U* b, const U* uin, const T* e, U* uout, T* r,
                       bool with_bnorm = false) {
@@ -753,24 +753,18 @@ mg_status refine_step(mg_handle* h, const U* b, const U* uin, const T* e, U* uou
     const double bytes =
         double(d.n) * (sizeof(U) + sizeof(T) + (uin ? sizeof(U) : 0) +
                        (uin || e ? sizeof(U) : 0) + (e ? sizeof(T) + sizeof(U) : 0));
-    int nb = 0;
     {
         Phase ph(h, 1);
         {
             Launch g(h, MG_K_RESIDUAL64, 0, bytes);
-            nb = mgk::residual_update<U, T, T>(view<U>(d), b, uin, e, uout, r, h->partials,
-                                               with_bnorm ? h->partials + h->max_partials
-                                                          : nullptr,
-                                               h->stream);
+            mgk::residual_update<U, T, T>(view<U>(d), b, uin, e, uout, r, h->partials,
+                                          with_bnorm ? h->partials + h->max_partials : nullptr,
+                                          h->blocks_done, h->host_scalar, h->stream);
         }
         MG_TRY(check_launch(h, "residual_update"));
-        {
-            Launch g(h, MG_K_OTHER, 0, double(nb) * 8 * (with_bnorm ? 2 : 1));
-            mgk::sum_partials(h->partials, nb, h->scalar, h->stream, with_bnorm ? 2 : 1,
-                              h->max_partials);
-        }
     }
-    return post_scalar(h);
+    HIP_TRY(h, hipEventRecord(h->scalar_ready, h->stream));
+    return MG_OK;
 }
 
 // ||r|| of the last step (and ||b|| into bnorm when given, for a step
@@ -1049,6 +1043,7 @@ mg_status build(mg_handle* h, const double* alpha) {
                                  mgk::blocks_for(f.plane), 8192});
     MG_TRY(dalloc(h, &h->partials, 2 * size_t(h->max_partials)));
     MG_TRY(dalloc(h, &h->scalar, 2));
+    MG_TRY(upload(h, &h->blocks_done, std::vector<unsigned>(1, 0u)));
     MG_TRY(dalloc(h, &h->u_alt, f.n));
     MG_TRY(dalloc(h, &h->u_alt2, f.n));
     HIP_TRY(h, hipHostMalloc((void**)&h->host_scalar, 2 * sizeof(double), hipHostMallocDefault));

@@ -15,13 +15,24 @@
 // the old neighbours, so the new iterate overwrites them in place) and after
 // the new iterate is written.
 //
-// UNIT: the block solves for U unit vectors at once, U copies of the level
-// side by side in its lanes and LDS, and writes U rows of the transposed
-// matrix. With all of its U * columns lanes packed, a block wastes no
-// wavefront on a ragged tail, and the pivots and couplings are shared. The
-// horizontal and vertical couplings are products of a layer and a row factor
-// (the metric terms separate); the row factors stay in registers and the
-// layer factors are scalar loads, so no coupling is read from LDS.
+// UNIT: the block solves for U unit vectors at once, U copies of a layer side
+// by side in its lanes and LDS, and writes U rows of the matrix (which is
+// symmetric, as H is: x = C f with C = sum_k (I - omega H_z^{-1} H)^k omega
+// H_z^{-1}). With all of its U * columns lanes packed, a block wastes no
+// wavefront on a ragged tail, and the pivots are shared. The couplings are
+// products of a layer and a row factor (the metric terms separate): layer k's
+// unknowns are scaled by the square root of its horizontal factor h_k, which
+// takes that factor out of the stencil and leaves the matrix symmetric, and
+// the eliminated values by the row's vertical factor; the row factors stay in
+// registers and the vertical layer factors in a lane each, so no coupling is
+// read from LDS.
+//
+// Measured, matrix of 5,040 cells in columns of 70 layers: 1.52 ms (6.94 with
+// one unit vector per block and the couplings in LDS; 1.68 with unscaled
+// unknowns, whose steps take half as many instructions again; 1.54 with loads
+// two steps ahead and not three). The vector units are busy half of that and
+// LDS for two fifths: what bounds it is the steps' latency, with the eight
+// wavefronts that registers and LDS hold.
 #include "device.hpp"
 
 namespace mgk {
@@ -34,8 +45,10 @@ using namespace dev;
 constexpr int kCoarseThreads = 512;
 
 // Steps whose LDS loads are in flight ahead of the ones being solved.
-template <typename T, int NS>
-constexpr int coarse_ahead() { return std::is_same<T, float>::value && NS <= 44 ? 4 : 2; }
+template <typename T, int NS, bool UNIT>
+constexpr int coarse_ahead() {
+    return std::is_same<T, float>::value && NS <= 44 ? 4 : (UNIT ? 3 : 2);
+}
 
 // The LDS loads of one step: the four neighbours, and (not UNIT) the
 // right-hand side and the couplings of the layer, cn the vertical one to the
@@ -59,7 +72,7 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse_sweeps(
     extern __shared__ unsigned char smem_raw[];
     const int P = int(L.plane), nz = L.nz, nJ = L.nJ, n = P * nz;
     const int H = int(blockDim.x) >> 1;          // lanes of one half (whole wavefronts)
-    T* sx = reinterpret_cast<T*>(smem_raw);      // [U][nz][P] iterate
+    T* sx = reinterpret_cast<T*>(smem_raw);      // [nz][U][P] iterate
     T* xch = sx + size_t(U) * n;                 // [3][H] exchange
     T* sp = xch + 3 * H;                         // [nz][P] pivots (not IPREG)
     T* sf = sp + (IPREG ? 0 : n);                // [nz][P] right-hand side (not UNIT)
@@ -68,7 +81,10 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse_sweeps(
     T* str = sth + (UNIT ? 0 : nz * (nJ + 1));   // [nz+1][nJ] (not UNIT)
     for (int t = threadIdx.x; t < U * n; t += blockDim.x) sx[t] = T(0);
     if constexpr (!IPREG)
-        for (int t = threadIdx.x; t < n; t += blockDim.x) sp[t] = L.invp[t];
+        for (int t = threadIdx.x; t < n; t += blockDim.x) {
+            sp[t] = L.invp[t];
+            if constexpr (UNIT) sp[t] *= T(sep.h[t / P]) * T(sep.gr[(t % P) / L.nI]);
+        }
     constexpr bool STAGE = !UNIT && !(std::is_same<T, float>::value && NS <= 24);
     if constexpr (STAGE) {
         for (int t = threadIdx.x; t < n; t += blockDim.x) sf[t] = f[t];
@@ -84,9 +100,10 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse_sweeps(
     const int u = active ? u0 : 0, col = active ? idx - u0 * P : 0;
     const Nb b = neighbours<false>(uint32_t(col), L.nI, nJ);
     const int J = b.J;
-    // UNIT: this lane's right-hand side is 1 in layer kf (none if -1)
-    const int row = int(blockIdx.x) * U + u;
-    const int kf = UNIT && row < n && row % P == col ? row / P : -1;
+    // UNIT: the block's unit vectors are 1 in layer ku, columns cu .. cu + U - 1
+    const int per_layer = UNIT ? (P + U - 1) / U : 1;
+    const int ku = UNIT ? int(blockIdx.x) / per_layer : -1;
+    const int cu = UNIT ? (int(blockIdx.x) - ku * per_layer) * U : 0;
     // row factors of the couplings (UNIT)
     const T gl = UNIT ? T(sep.gl[J]) : T(0), gs = UNIT ? T(sep.gt[J]) : T(0),
             gn = UNIT ? T(sep.gt[J + 1]) : T(0), gr = UNIT ? T(sep.gr[J]) : T(0);
@@ -101,13 +118,20 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse_sweeps(
         for (int t = 0; t < NS; ++t) {
             const int k = k0 + (t < own ? t : 0) * ks;
             ip[t] = L.invp[size_t(k) * size_t(P) + col];
+            if constexpr (UNIT) ip[t] *= T(sep.h[k]) * gr;
         }
     }
-    // UNIT: the layer factors by step, step t's in lane t (read back with a
-    // readlane: scalar loads in the chain would each be waited for)
+    // UNIT: the vertical couplings of the scaled unknowns by step, step t's in
+    // lane t (read back with a readlane: scalar loads in the chain would each
+    // be waited for)
     const int lane = int(threadIdx.x & 63u);
-    const int kl = k0 + (lane < own ? lane : 0) * ks;
-    const T hv = UNIT ? T(sep.h[kl]) : T(0), vv = UNIT ? T(sep.v[top ? kl : kl + 1]) : T(0);
+    T vv = T(0), fu = T(0);
+    if constexpr (UNIT) {
+        const int kl = k0 + (lane < own ? lane : 0) * ks;
+        const int kn = kl + ks < 0 ? 0 : clampk(kl + ks, nz);
+        vv = T(sep.v[top ? kl : kl + 1]) / sqrt(T(sep.h[kl]) * T(sep.h[kn]));
+        fu = active && col == cu + u ? T(1) / sqrt(T(sep.h[ku])) : T(0);
+    }
     // not UNIT, FP32: couplings times pivots kept for the back-substitution
     constexpr bool KEEPCB = !UNIT && std::is_same<T, float>::value;
     // not UNIT, FP32, short columns: what no sweep changes stays in registers
@@ -126,9 +150,16 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse_sweeps(
             hc[t] = L.Tr[(top ? k : k + 1) * nJ + J];
         }
     }
-    const T keep = T(1) - omega;
-    const int xb = u * n;
-    constexpr int D = coarse_ahead<T, NS>();
+    const T keep = T(1) - omega, damp = UNIT ? omega / gr : omega;
+    // byte addresses in the iterate: this column and its neighbours, layer 0
+    const uint32_t xb = uint32_t(u) * uint32_t(P);
+    const uint32_t xc = (xb + uint32_t(col)) * uint32_t(sizeof(T)),
+                   xw = (xb + b.w) * uint32_t(sizeof(T)), xe = (xb + b.e) * uint32_t(sizeof(T)),
+                   xs = (xb + b.s) * uint32_t(sizeof(T)), xn = (xb + b.n) * uint32_t(sizeof(T));
+    auto at = [&](uint32_t base, uint32_t off) -> T& {
+        return *reinterpret_cast<T*>(smem_raw + (base + off));
+    };
+    constexpr int D = coarse_ahead<T, NS, UNIT>();
     constexpr int NC = (NS + D - 1) / D;
     __syncthreads();
 
@@ -136,20 +167,23 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse_sweeps(
         // opaque copies, once per chunk, of what the steps' addresses and role
         // decisions depend on: they are formed where they are used, not
         // hoisted out of the loops into hundreds of registers
-        int pl = P, kb = k0, ow = own, el = elim;
-        auto opaque = [&]() { asm volatile("" : "+s"(pl), "+s"(kb), "+s"(ow), "+s"(el)); };
-        T hs = hv, vs = vv;
-        if constexpr (UNIT) asm volatile("" : "+v"(hs), "+v"(vs));
+        int pl = P, xl = U * P * int(sizeof(T)), kb = k0, ow = own, el = elim;
+        auto opaque = [&]() {
+            asm volatile("" : "+s"(pl), "+s"(xl), "+s"(kb), "+s"(ow), "+s"(el));
+        };
+        T vs = vv;
+        if constexpr (UNIT) asm volatile("" : "+v"(vs));
         // steps past a half's layers load a real layer; what they compute is
         // discarded
         auto layer_of = [&](int t) { return kb + (t < NS - G || t < ow ? t : 0) * ks; };
         auto fetch = [&](int t) {
             CoarseNb<T> r;
-            const int k = layer_of(t), o = xb + k * pl;
-            r.w = sx[o + int(b.w)];
-            r.e = sx[o + int(b.e)];
-            r.s = sx[o + int(b.s)];
-            r.n = sx[o + int(b.n)];
+            const int k = layer_of(t);
+            const uint32_t o = uint32_t(k * xl);
+            r.w = at(xw, o);
+            r.e = at(xe, o);
+            r.s = at(xs, o);
+            r.n = at(xn, o);
             if constexpr (!IPREG) r.ip = sp[k * pl + col];
             if constexpr (!UNIT && !HOLD) {
                 r.f = sf[k * pl + col];
@@ -163,7 +197,7 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse_sweeps(
         auto fetch_back = [&](int t) {
             CoarseBack<T> r;
             const int k = layer_of(t);
-            r.x = sx[xb + k * pl + col];
+            r.x = at(xc, uint32_t(k * xl));
             if constexpr (!IPREG) r.ip = sp[k * pl + col];
             if constexpr (!UNIT && !KEEPCB) r.cn = str[(top ? k : k + 1) * nJ + J];
             return r;
@@ -189,9 +223,9 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse_sweeps(
                 const CoarseNb<T>& r = q[c & 1][d];
                 T sv, cn;
                 if constexpr (UNIT) {
-                    sv = lane_value(hs, t) * (gl * (r.w + r.e) + gs * r.s + gn * r.n) +
-                         (kb + t * ks == kf ? T(1) : T(0));
-                    cn = lane_value(vs, t) * gr;
+                    const T one = kb + t * ks == ku ? T(1) : T(0);   // wave-uniform
+                    sv = gl * (r.w + r.e) + one * fu + gs * r.s + gn * r.n;
+                    cn = lane_value(vs, t);
                 } else if constexpr (HOLD) {
                     const int h = HOLD ? t : 0;
                     sv = hf[h] + hl[h] * (r.w + r.e) + hs_[h] * r.s + hn[h] * r.n;
@@ -200,7 +234,7 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse_sweeps(
                     sv = r.f + r.tl * (r.w + r.e) + r.ts * r.s + r.tn * r.n;
                     cn = r.cn;
                 }
-                const T p = IPREG ? ip[IPREG ? t : 0] : r.ip;
+                const T p = IPREG ? ip[IPREG ? t : 0] : r.ip;   // (UNIT: scaled)
                 sv += cp * vp;
                 y[t] = sv * p;
                 if constexpr (KEEPCB) cb[t] = cn * p;
@@ -250,12 +284,12 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse_sweeps(
                         k_ = cb[t];
                     } else {
                         const T p = IPREG ? ip[IPREG ? t : 0] : r.ip;
-                        if constexpr (UNIT) k_ = lane_value(vs, t) * gr * p;
+                        if constexpr (UNIT) k_ = lane_value(vs, t) * p;
                         else k_ = r.cn * p;
                     }
                     if (t < NS - G - 1 || t < el) z = y[t] + k_ * z;
-                    const T out = omega * z + keep * r.x;
-                    if (t < NS - G || t < ow) sx[xb + (kb + t * ks) * pl + col] = out;
+                    const T out = damp * z + keep * r.x;
+                    if (t < NS - G || t < ow) at(xc, uint32_t((kb + t * ks) * xl)) = out;
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -263,12 +297,12 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse_sweeps(
         __syncthreads();
     }
     if constexpr (UNIT) {
-        // rows blockIdx.x * U .. of the transposed matrix, n values each
-        const long long left = (long long)(n - int(blockIdx.x) * U) * n;
-        const int count = left < (long long)U * n ? int(left) : U * n;
-        const size_t base = size_t(blockIdx.x) * size_t(U) * size_t(n);
+        // the unit vectors' rows of the matrix, n values each
+        const int count = (P - cu < U ? P - cu : U) * n;
+        const size_t base = (size_t(ku) * size_t(P) + size_t(cu)) * size_t(n);
         for (int t = threadIdx.x; t < count; t += blockDim.x) {
-            const T v = sx[t];
+            const int uu = t / n, kk = (t - uu * n) / P, cc = t - uu * n - kk * P;
+            const T v = sx[(kk * U + uu) * P + cc] / sqrt(T(sep.h[kk]));
             xout[base + t] = v;
             xout32[base + t] = float(v);
         }
@@ -356,15 +390,15 @@ bool coarse_basis_fits(long long plane, int nJ, int nz, size_t max_lds) {
            basis_vectors(plane, nJ, nz, max_lds) > 0;
 }
 
-bool coarse_basis(const LevelView<double>& L, const SepView& sep, double* Ct, float* Ct32,
+bool coarse_basis(const LevelView<double>& L, const SepView& sep, double* C, float* C32,
                   double omega, int sweeps, size_t max_lds, hipStream_t s) {
     const long long n = L.plane * L.nz;
     if (n < 1 || !coarse_basis_fits(L.plane, L.nJ, L.nz, max_lds)) return false;
     const int U = basis_vectors(L.plane, L.nJ, L.nz, max_lds);
     bool done = false;
     with_half((L.nz + 1) / 2, [&](auto ns, auto g) {
-        done = launch<double, decltype(ns)::value, decltype(g)::value, true>(L, sep, nullptr, Ct, Ct32, omega, sweeps,
-                                                         U, int((n + U - 1) / U), s);
+        done = launch<double, decltype(ns)::value, decltype(g)::value, true>(L, sep, nullptr, C, C32, omega, sweeps,
+                                                         U, int((L.plane + U - 1) / U * L.nz), s);
     });
     return done;
 }

@@ -38,28 +38,6 @@ __global__ __launch_bounds__(kBlock) void k_dense_matvec(const T* __restrict__ A
     if (lane == 0) x[row] = s;
 }
 
-// 32 x 32 tiles through LDS (padded against bank conflicts); 256 threads as
-// 32 columns x 8 rows.
-__global__ __launch_bounds__(kBlock) void k_transpose(const double* __restrict__ A,
-                                                      double* __restrict__ B,
-                                                      float* __restrict__ B32, long long n) {
-    __shared__ double tile[32][33];
-    const long long c0 = (long long)blockIdx.x * 32, r0 = (long long)blockIdx.y * 32;
-    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-    for (int r = ty; r < 32; r += 8) {
-        const long long i = r0 + r, j = c0 + tx;
-        if (i < n && j < n) tile[r][tx] = A[i * n + j];
-    }
-    __syncthreads();
-    for (int r = ty; r < 32; r += 8) {
-        const long long i = c0 + r, j = r0 + tx;
-        if (i < n && j < n) {
-            B[i * n + j] = tile[tx][r];
-            B32[i * n + j] = float(tile[tx][r]);
-        }
-    }
-}
-
 }  // namespace
 
 template <typename T>
@@ -67,11 +45,6 @@ void dense_matvec(const T* A, long long n, const T* f, T* x, hipStream_t s) {
     constexpr int rows_per_block = kBlock / 64;
     const long long nb = (n + rows_per_block - 1) / rows_per_block;
     k_dense_matvec<T><<<int(nb), kBlock, 0, s>>>(A, n, f, x);
-}
-
-void transpose_square(const double* A, double* B, float* B32, long long n, hipStream_t s) {
-    const unsigned t = unsigned((n + 31) / 32);
-    k_transpose<<<dim3(t, t), kBlock, 0, s>>>(A, B, B32, n);
 }
 
 template void dense_matvec<float>(const float*, long long, const float*, float*, hipStream_t);

@@ -100,21 +100,17 @@ template <typename T>
 bool coarse_solve(const LevelView<T>& L, const T* f, T* x, T omega, int sweeps, size_t max_lds,
                   hipStream_t s);
 
-// The coarsest-level solve is a linear map x = C f of the level's n cells.
-// coarse_basis writes C^T, row by row (row j is the solve applied to the
-// j-th unit vector), computed in FP64, into Ct and rounded to FP32 into Ct32
-// (n*n values each). Returns false, launching nothing, where the level has
+// The coarsest-level solve is a linear map x = C f of the level's n cells, and
+// a symmetric one. coarse_basis writes C row by row (row j is the solve applied
+// to the j-th unit vector), computed in FP64, into C and rounded to FP32 into
+// C32 (n*n values each). Returns false, launching nothing, where the level has
 // more than kDenseCoarseMax cells or kDenseCoarseColumns columns or does not
 // fit in max_lds bytes of LDS (coarse_basis_fits).
 constexpr long long kDenseCoarseMax = 6144;
 constexpr long long kDenseCoarseColumns = 128;
 bool coarse_basis_fits(long long plane, int nJ, int nz, size_t max_lds);
-bool coarse_basis(const LevelView<double>& L, const SepView& sep, double* Ct, float* Ct32,
+bool coarse_basis(const LevelView<double>& L, const SepView& sep, double* C, float* C32,
                   double omega, int sweeps, size_t max_lds, hipStream_t s);
-
-// B = A^T for n x n row-major matrices (A and B distinct), and B32 the same
-// rounded to FP32.
-void transpose_square(const double* A, double* B, float* B32, long long n, hipStream_t s);
 
 // x = A f for an n x n row-major matrix: one wavefront per row, partial sums
 // in a fixed order (results are reproducible).

@@ -76,17 +76,17 @@ struct ProfRec {
     bool zero_pair = false;
 };
 
-// Explicit matrix C of the coarsest-level solve (x = C f), and C^T for the
-// transposed cycle, in both precisions; formed for the current coefficients,
-// omega and number of sweeps.
+// Explicit matrix C of the coarsest-level solve (x = C f; C is symmetric) in
+// both precisions; formed for the current coefficients, omega and number of
+// sweeps.
 struct DenseCoarse {
     bool enabled = false;   // the coarsest level is small enough
-    bool valid = false;     // matrices match the current coefficients/options
+    bool valid = false;     // they match the current coefficients/options
     long long n = 0;
     int sweeps = -1;
     double omega = 0;
-    double *C64 = nullptr, *Ct64 = nullptr;
-    float *C32 = nullptr, *Ct32 = nullptr;
+    double* C64 = nullptr;
+    float* C32 = nullptr;
 };
 
 }  // namespace
@@ -254,14 +254,9 @@ template <>
 Work<double>& work<double>(DevLevel& d) { return d.w64; }
 
 template <typename T>
-const T* dense_C(const mg_handle* h, bool transposed);
-template <>
-const float* dense_C<float>(const mg_handle* h, bool transposed) {
-    return transposed ? h->dense.Ct32 : h->dense.C32;
-}
-template <>
-const double* dense_C<double>(const mg_handle* h, bool transposed) {
-    return transposed ? h->dense.Ct64 : h->dense.C64;
+const T* dense_C(const mg_handle* h) {
+    if constexpr (std::is_same<T, float>::value) return h->dense.C32;
+    else return h->dense.C64;
 }
 
 template <typename T>
@@ -543,7 +538,7 @@ mg_status vcycle(mg_handle* h, int l, const T* f, T** result) {
             // the coarse solve's explicit matrix: one matrix-vector product
             {
                 Launch g(h, MG_K_COARSE, l, double(d.n) * (d.n + 2) * sizeof(T));
-                mgk::dense_matvec<T>(dense_C<T>(h, false), d.n, f, cur, h->stream);
+                mgk::dense_matvec<T>(dense_C<T>(h), d.n, f, cur, h->stream);
             }
             MG_TRY(check_launch(h, "dense coarse solve"));
             *result = cur;
@@ -681,7 +676,7 @@ mg_status vcycle_adj(mg_handle* h, int l, const T* f, T** result) {
         if (h->dense.valid) {
             {
                 Launch g(h, MG_K_COARSE, l, double(d.n) * (d.n + 2) * sizeof(T));
-                mgk::dense_matvec<T>(dense_C<T>(h, true), d.n, f, cur, h->stream);
+                mgk::dense_matvec<T>(dense_C<T>(h), d.n, f, cur, h->stream);
             }
             MG_TRY(check_launch(h, "dense transposed coarse solve"));
             *result = cur;
@@ -937,22 +932,21 @@ mg_status outer(mg_handle* h, const double* b, double* u, double tol, mg_stats* 
     return status;
 }
 
-// Form the coarsest solve's matrices for the current pivots, omega and
-// number of sweeps: C^T from the solves of the unit vectors (FP64), C by
-// transposition, FP32 copies of both.
+// Form the coarsest solve's matrix for the current pivots, omega and number of
+// sweeps from the solves of the unit vectors (FP64), and its FP32 copy. The
+// sweeps take one factor, so it is symmetric: row j is the solve of the j-th
+// unit vector, and the transposed cycle uses the same matrix.
 mg_status rebuild_dense(mg_handle* h) {
     DenseCoarse& D = h->dense;
     D.valid = false;
     if (!D.enabled) return MG_OK;
     const DevLevel& c = h->lv.back();
-    if (!mgk::coarse_basis(view<double>(c), {c.fh, c.fv, c.flam, c.fth, c.fr}, D.Ct64, D.Ct32,
+    if (!mgk::coarse_basis(view<double>(c), {c.fh, c.fv, c.flam, c.fth, c.fr}, D.C64, D.C32,
                            h->opt.omega, h->opt.coarse_sweeps, h->max_lds, h->stream)) {
         D.enabled = false;   // does not fit: keep the sweeps
         return MG_OK;
     }
     MG_TRY(check_launch(h, "coarse_basis"));
-    mgk::transpose_square(D.Ct64, D.C64, D.C32, D.n, h->stream);
-    MG_TRY(check_launch(h, "transpose"));
     D.sweeps = h->opt.coarse_sweeps;
     D.omega = h->opt.omega;
     D.valid = true;
@@ -1064,9 +1058,7 @@ mg_status build(mg_handle* h, const double* alpha) {
         if (D.enabled) {
             const size_t nn = size_t(c.n) * size_t(c.n);
             MG_TRY(dalloc(h, &D.C64, nn));
-            MG_TRY(dalloc(h, &D.Ct64, nn));
             MG_TRY(dalloc(h, &D.C32, nn));
-            MG_TRY(dalloc(h, &D.Ct32, nn));
         }
     }
     return set_coeffs(h, alpha);

@@ -27,12 +27,14 @@
 // registers and the vertical layer factors in a lane each, so no coupling is
 // read from LDS.
 //
-// Measured, matrix of 5,040 cells in columns of 70 layers: 1.52 ms (6.94 with
+// Measured, matrix of 5,040 cells in columns of 70 layers: 1.50 ms (6.94 with
 // one unit vector per block and the couplings in LDS; 1.68 with unscaled
-// unknowns, whose steps take half as many instructions again; 1.54 with loads
-// two steps ahead and not three). The vector units are busy half of that and
-// LDS for two fifths: what bounds it is the steps' latency, with the eight
-// wavefronts that registers and LDS hold.
+// unknowns, whose steps take half as many instructions again). The vector
+// units are busy half of that and LDS for two fifths: what bounds it is the
+// steps' latency, with the eight wavefronts that registers and LDS hold. Plain
+// solve, 40 sweeps of 252 columns of 38 layers in FP32: 54 us (101 with the
+// couplings in LDS, 75 with the iterate by layer, whose addresses each step
+// computes), 1.35 us per sweep on one CU, latency again.
 #include "device.hpp"
 
 namespace mgk {
@@ -44,11 +46,27 @@ using namespace dev;
 // 256 VGPRs, which FP64 needs for its pivots and forward values).
 constexpr int kCoarseThreads = 512;
 
-// Steps whose LDS loads are in flight ahead of the ones being solved.
+// Short FP32 columns of a plain solve: what no sweep changes (right-hand side
+// and couplings) stays in registers.
+template <typename T, int NS, bool UNIT>
+constexpr bool coarse_hold() { return !UNIT && std::is_same<T, float>::value && NS <= 24; }
+
+// Steps whose LDS loads are in flight ahead of the ones being solved. (FP32
+// columns of 38 layers: 54 us with 2, 58 with 4, 61 with 1 or 5. Unit vectors,
+// 70 layers: 1.50 ms with 3, 1.60 with 2, 1.56 with 4.)
 template <typename T, int NS, bool UNIT>
 constexpr int coarse_ahead() {
-    return std::is_same<T, float>::value && NS <= 44 ? 4 : (UNIT ? 3 : 2);
+    if (UNIT) return 3;
+    return std::is_same<T, float>::value && NS <= 44 && !coarse_hold<T, NS, UNIT>() ? 4 : 2;
 }
+
+// Whether the iterate lies in LDS by half and step, kStride values per step
+// whatever the block's lanes: then a step's addresses are immediate offsets.
+// (Where that fits: all that coarse_hold() covers, and FP64 columns up to 36
+// steps. Otherwise by layer, as many values as there are lanes.)
+constexpr int kStride = kCoarseThreads / 2;
+template <typename T, int NS, bool UNIT>
+constexpr bool fixed_stride() { return UNIT ? NS <= 36 : coarse_hold<T, NS, UNIT>(); }
 
 // The LDS loads of one step: the four neighbours, and (not UNIT) the
 // right-hand side and the couplings of the layer, cn the vertical one to the
@@ -72,20 +90,22 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse_sweeps(
     extern __shared__ unsigned char smem_raw[];
     const int P = int(L.plane), nz = L.nz, nJ = L.nJ, n = P * nz;
     const int H = int(blockDim.x) >> 1;          // lanes of one half (whole wavefronts)
-    T* sx = reinterpret_cast<T*>(smem_raw);      // [nz][U][P] iterate
-    T* xch = sx + size_t(U) * n;                 // [3][H] exchange
+    constexpr bool FIXED = fixed_stride<T, NS, UNIT>();
+    const int nx = FIXED ? 2 * NS * kStride : U * n;
+    T* sx = reinterpret_cast<T*>(smem_raw);      // [2][NS][kStride] or [nz][U][P] iterate
+    T* xch = sx + nx;                            // [3][H] exchange
     T* sp = xch + 3 * H;                         // [nz][P] pivots (not IPREG)
     T* sf = sp + (IPREG ? 0 : n);                // [nz][P] right-hand side (not UNIT)
     T* stl = sf + (UNIT ? 0 : n);                // [nz][nJ] (not UNIT)
     T* sth = stl + (UNIT ? 0 : nz * nJ);         // [nz][nJ+1] (not UNIT)
     T* str = sth + (UNIT ? 0 : nz * (nJ + 1));   // [nz+1][nJ] (not UNIT)
-    for (int t = threadIdx.x; t < U * n; t += blockDim.x) sx[t] = T(0);
+    for (int t = threadIdx.x; t < nx; t += blockDim.x) sx[t] = T(0);
     if constexpr (!IPREG)
         for (int t = threadIdx.x; t < n; t += blockDim.x) {
             sp[t] = L.invp[t];
             if constexpr (UNIT) sp[t] *= T(sep.h[t / P]) * T(sep.gr[(t % P) / L.nI]);
         }
-    constexpr bool STAGE = !UNIT && !(std::is_same<T, float>::value && NS <= 24);
+    constexpr bool HOLD = coarse_hold<T, NS, UNIT>(), STAGE = !UNIT && !HOLD;
     if constexpr (STAGE) {
         for (int t = threadIdx.x; t < n; t += blockDim.x) sf[t] = f[t];
         for (int t = threadIdx.x; t < nz * nJ; t += blockDim.x) stl[t] = L.Tlam[t];
@@ -134,9 +154,6 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse_sweeps(
     }
     // not UNIT, FP32: couplings times pivots kept for the back-substitution
     constexpr bool KEEPCB = !UNIT && std::is_same<T, float>::value;
-    // not UNIT, FP32, short columns: what no sweep changes stays in registers
-    // (right-hand side and couplings), so a step reads only its neighbours
-    constexpr bool HOLD = KEEPCB && NS <= 24;
     T hf[HOLD ? NS : 1], hl[HOLD ? NS : 1], hs_[HOLD ? NS : 1], hn[HOLD ? NS : 1],
         hc[HOLD ? NS : 1];
     if constexpr (HOLD) {
@@ -151,8 +168,11 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse_sweeps(
         }
     }
     const T keep = T(1) - omega, damp = UNIT ? omega / gr : omega;
-    // byte addresses in the iterate: this column and its neighbours, layer 0
-    const uint32_t xb = uint32_t(u) * uint32_t(P);
+    // byte addresses in the iterate: this column and its neighbours, first step
+    // (FIXED) or layer 0
+    const uint32_t xb = uint32_t(u) * uint32_t(P) + (FIXED && top ? NS * kStride : 0);
+    // UNIT: this half's step with the unit values (-1: none)
+    const int tu = !UNIT ? -1 : (top ? (ku >= m ? nz - 1 - ku : -1) : (ku < m ? ku : -1));
     const uint32_t xc = (xb + uint32_t(col)) * uint32_t(sizeof(T)),
                    xw = (xb + b.w) * uint32_t(sizeof(T)), xe = (xb + b.e) * uint32_t(sizeof(T)),
                    xs = (xb + b.s) * uint32_t(sizeof(T)), xn = (xb + b.n) * uint32_t(sizeof(T));
@@ -167,19 +187,24 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse_sweeps(
         // opaque copies, once per chunk, of what the steps' addresses and role
         // decisions depend on: they are formed where they are used, not
         // hoisted out of the loops into hundreds of registers
-        int pl = P, xl = U * P * int(sizeof(T)), kb = k0, ow = own, el = elim;
+        int pl = P, xl = U * P * int(sizeof(T)), kb = k0, ow = own, el = elim,
+            un = tu;
         auto opaque = [&]() {
-            asm volatile("" : "+s"(pl), "+s"(xl), "+s"(kb), "+s"(ow), "+s"(el));
+            asm volatile("" : "+s"(pl), "+s"(xl), "+s"(kb), "+s"(ow), "+s"(el), "+s"(un));
         };
         T vs = vv;
         if constexpr (UNIT) asm volatile("" : "+v"(vs));
         // steps past a half's layers load a real layer; what they compute is
         // discarded
         auto layer_of = [&](int t) { return kb + (t < NS - G || t < ow ? t : 0) * ks; };
+        auto offset_of = [&](int t) -> uint32_t {
+            if constexpr (FIXED) return uint32_t(t * kStride) * uint32_t(sizeof(T));
+            else return uint32_t(layer_of(t) * xl);
+        };
         auto fetch = [&](int t) {
             CoarseNb<T> r;
             const int k = layer_of(t);
-            const uint32_t o = uint32_t(k * xl);
+            const uint32_t o = offset_of(t < NS ? t : NS - 1);
             r.w = at(xw, o);
             r.e = at(xe, o);
             r.s = at(xs, o);
@@ -197,7 +222,7 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse_sweeps(
         auto fetch_back = [&](int t) {
             CoarseBack<T> r;
             const int k = layer_of(t);
-            r.x = at(xc, uint32_t(k * xl));
+            r.x = at(xc, offset_of(t < NS ? t : NS - 1));
             if constexpr (!IPREG) r.ip = sp[k * pl + col];
             if constexpr (!UNIT && !KEEPCB) r.cn = str[(top ? k : k + 1) * nJ + J];
             return r;
@@ -223,7 +248,7 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse_sweeps(
                 const CoarseNb<T>& r = q[c & 1][d];
                 T sv, cn;
                 if constexpr (UNIT) {
-                    const T one = kb + t * ks == ku ? T(1) : T(0);   // wave-uniform
+                    const T one = t == un ? T(1) : T(0);   // wave-uniform
                     sv = gl * (r.w + r.e) + one * fu + gs * r.s + gn * r.n;
                     cn = lane_value(vs, t);
                 } else if constexpr (HOLD) {
@@ -289,38 +314,34 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse_sweeps(
                     }
                     if (t < NS - G - 1 || t < el) z = y[t] + k_ * z;
                     const T out = damp * z + keep * r.x;
-                    if (t < NS - G || t < ow) at(xc, uint32_t((kb + t * ks) * xl)) = out;
+                    if (t < NS - G || t < ow) at(xc, offset_of(t)) = out;
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
         __syncthreads();
     }
+    auto place = [&](int k, int c) {
+        if constexpr (FIXED) return (k < m ? k : NS + nz - 1 - k) * kStride + c;
+        else return k * U * P + c;
+    };
     if constexpr (UNIT) {
         // the unit vectors' rows of the matrix, n values each
         const int count = (P - cu < U ? P - cu : U) * n;
         const size_t base = (size_t(ku) * size_t(P) + size_t(cu)) * size_t(n);
         for (int t = threadIdx.x; t < count; t += blockDim.x) {
             const int uu = t / n, kk = (t - uu * n) / P, cc = t - uu * n - kk * P;
-            const T v = sx[(kk * U + uu) * P + cc] / sqrt(T(sep.h[kk]));
+            const T v = sx[place(kk, uu * P + cc)] / sqrt(T(sep.h[kk]));
             xout[base + t] = v;
             xout32[base + t] = float(v);
         }
     } else {
-        for (int t = threadIdx.x; t < n; t += blockDim.x) xout[t] = sx[t];
+        for (int t = threadIdx.x; t < n; t += blockDim.x)
+            xout[t] = sx[FIXED ? place(t / P, t % P) : t];
     }
 }
 
 inline int lanes64(long long c) { return int((c + 63) / 64 * 64); }
-
-// LDS values of a block (see the kernel's layout).
-inline size_t coarse_values(long long plane, int nJ, int nz, int U, bool ipreg, bool unit) {
-    const size_t n = size_t(plane) * size_t(nz);
-    const size_t tables =
-        unit ? 0 : size_t(nz) * nJ + size_t(nz) * (nJ + 1) + size_t(nz + 1) * nJ;
-    return size_t(U) * n + 3 * size_t(lanes64(plane * U)) + (ipreg ? 0 : n) + (unit ? 0 : n) +
-           tables;
-}
 
 // Pivots in registers up to 36 steps in FP64 (72 VGPRs beside as many for
 // the forward values), up to 64 in FP32.
@@ -328,16 +349,30 @@ template <typename T>
 constexpr bool pivots_in_registers(int ns) {
     return std::is_same<T, float>::value || ns <= 36;
 }
-template <typename T>
-bool pivots_in_registers_for(int nz) {
-    return std::is_same<T, float>::value || (nz + 1) / 2 <= 36;
+
+// LDS values of a block (see the kernel's layout).
+template <typename T, int NS, bool UNIT>
+size_t coarse_values(long long plane, int nJ, int nz, int U) {
+    const size_t n = size_t(plane) * size_t(nz);
+    const size_t staged = size_t(nz) * nJ + size_t(nz) * (nJ + 1) + size_t(nz + 1) * nJ + n;
+    return (fixed_stride<T, NS, UNIT>() ? size_t(2 * NS * kStride) : size_t(U) * n) +
+           3 * size_t(lanes64(plane * U)) + (pivots_in_registers<T>(NS) ? 0 : n) +
+           (UNIT || coarse_hold<T, NS, UNIT>() ? 0 : staged);
+}
+template <typename T, bool UNIT>
+size_t coarse_values_for(long long plane, int nJ, int nz, int U) {
+    size_t v = 0;
+    with_half((nz + 1) / 2, [&](auto ns, auto) {
+        v = coarse_values<T, decltype(ns)::value, UNIT>(plane, nJ, nz, U);
+    });
+    return v;
 }
 
 template <typename T, int NS, int G, bool UNIT>
 bool launch(const LevelView<T>& L, const SepView& sep, const T* f, T* x, float* x32, T omega,
             int sweeps, int U, int blocks, hipStream_t s) {
     constexpr bool IPREG = pivots_in_registers<T>(NS);
-    const size_t lds = coarse_values(L.plane, L.nJ, L.nz, U, IPREG, UNIT) * sizeof(T);
+    const size_t lds = coarse_values<T, NS, UNIT>(L.plane, L.nJ, L.nz, U) * sizeof(T);
     if (lds > 64 * 1024 &&
         hipFuncSetAttribute(reinterpret_cast<const void*>(&k_coarse_sweeps<T, NS, G, IPREG, UNIT>),
                             hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -355,8 +390,7 @@ bool launch(const LevelView<T>& L, const SepView& sep, const T* f, T* x, float* 
 template <typename T>
 bool coarse_solve_fits(long long plane, int nJ, int nz, size_t max_lds) {
     return 2 * lanes64(plane) <= kCoarseThreads &&
-           coarse_values(plane, nJ, nz, 1, pivots_in_registers_for<T>(nz), false) * sizeof(T) <=
-               max_lds;
+           coarse_values_for<T, false>(plane, nJ, nz, 1) * sizeof(T) <= max_lds;
 }
 
 template <typename T>
@@ -376,10 +410,9 @@ bool coarse_solve(const LevelView<T>& L, const T* f, T* x, T omega, int sweeps, 
 // more CUs instead).
 static int basis_vectors(long long plane, int nJ, int nz, size_t max_lds) {
     const long long n = plane * nz;
-    const bool ipreg = pivots_in_registers_for<double>(nz);
     int U = 0;
     while (2 * lanes64(plane * (U + 1)) <= kCoarseThreads &&
-           coarse_values(plane, nJ, nz, U + 1, ipreg, true) * sizeof(double) <= max_lds &&
+           coarse_values_for<double, true>(plane, nJ, nz, U + 1) * sizeof(double) <= max_lds &&
            (U == 0 || (U + 1) * 512LL <= n))
         ++U;
     return U;

@@ -176,7 +176,8 @@ enum {
     MG_K_RESIDUAL64 = 0,  /* FP64 update + residual + norm partials (fine)  */
     MG_K_SMOOTH,          /* block-Jacobi sweep from an iterate, all levels  */
     MG_K_RESTRICT,        /* fused residual + restriction                     */
-    MG_K_PROLONG,         /* bilinear prolongation (add)                      */
+    MG_K_PROLONG,         /* bilinear prolongation (add); on small levels of  */
+                          /* few layers part of a sweep and counted there     */
     MG_K_COARSE,          /* coarsest-level solve                             */
     MG_K_ADJOINT,         /* unused: the transposed cycle's kernels are     */
                           /* counted in the classes of their forward kinds  */

@@ -281,7 +281,24 @@ __device__ __forceinline__ double from_above(double edge, double src) {
     return __builtin_bit_cast(double, r);
 }
 
-// The same with 0 in the lane that has no source.
+// x + P xc at a cell: the two coarse rows' values c and cn (weights 3/4 and
+// 1/4), and the rows' weights w0 and w1. Contracted by hand: the same bits in
+// every kernel.
+template <typename T>
+__device__ __forceinline__ T prolonged(T x, T c0, T c0n, T c1, T c1n, T w0, T w1) {
+#pragma clang fp contract(off)
+    const T b0 = T(0.25) * c0n, b1 = T(0.25) * c1n;
+    const T h0 = __builtin_elementwise_fma(T(0.75), c0, b0);
+    const T h1 = __builtin_elementwise_fma(T(0.75), c1, b1);
+    return __builtin_elementwise_fma(w1, h1, __builtin_elementwise_fma(w0, h0, x));
+}
+// The coarse longitude a fine one interpolates from beside i / 2.
+__device__ __forceinline__ int prolong_neighbour(int i, int nIc) {
+    const int I = i >> 1;
+    return (i & 1) ? (I + 1 == nIc ? 0 : I + 1) : (I == 0 ? nIc - 1 : I - 1);
+}
+
+// from_below and from_above with 0 in the lane that has no source.
 __device__ __forceinline__ float from_below0(float src) {
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
                                          0, __builtin_bit_cast(int, src), 0x138, 0xf, 0xf, true));

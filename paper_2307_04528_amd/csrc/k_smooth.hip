@@ -54,11 +54,14 @@ constexpr size_t staged_lds_bytes(int nz, int pad) {
 }
 
 // NS: steps of a half column compiled for; a half has more than NS - G.
-template <typename T, int NS, int G, bool HAS_X>
+// PRO: the iterate is xin + P xc, formed as it is loaded: the first sweep after
+// a coarse-grid correction, without a launch of its own for P (4.7 us on any
+// small level; FP32 sweeps of 38 layers take 6.9 us instead of 4.8).
+template <typename T, int NS, int G, bool HAS_X, bool PRO>
 __global__ __launch_bounds__(64 * kStageWaves)
 __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2))) void k_smooth_staged(
     LevelView<T> L, const T* __restrict__ f, const T* __restrict__ xin, T* __restrict__ xout,
-    T omega, int wpr) {
+    T omega, int wpr, TransferView<T> X, const T* __restrict__ xc) {
     // products and sums are contracted by hand: the same bits in every variant
 #pragma clang fp contract(off)
     extern __shared__ unsigned char smem_raw[];
@@ -69,8 +72,37 @@ __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2))) void k_smooth_stage
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
     const int lane = int(threadIdx.x & 63u);
     const Seg g = segment(int(blockIdx.x), L.nI, nJ, wpr);
-    const NbB<T> b(g);
+    NbB<T> b(g);
     const int J = g.J;
+    // PRO: west and east of a column lie in the neighbour lanes, and one more
+    // column brings what the outer two lanes miss: west of lane 0's in the
+    // lower lanes, east of lane 63's in the upper. (A lane past the row's end,
+    // which stores nothing, takes the row's first column: the last one's east.)
+    // Coarse offsets of the four points: this column, south, north, outer.
+    uint32_t od = 0, oo[PRO ? 4 : 1][4];
+    T pw[PRO ? 4 : 1][2];
+    if constexpr (PRO) {
+        constexpr uint32_t S = sizeof(T);
+        const int nI = L.nI, i0 = (int(blockIdx.x) - J * wpr) * 64;
+        const int i = g.valid ? i0 + lane : 0;
+        const int io = lane < 32 ? (i0 == 0 ? nI - 1 : i0 - 1) : (i0 + 64 < nI ? i0 + 64 : 0);
+        od = uint32_t(J * nI + io) * S;
+        if (!g.valid) b.c = uint32_t(J * nI) * S;
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            const int j = p == 1 ? (J > 0 ? J - 1 : J) : (p == 2 ? (J < nJ - 1 ? J + 1 : J) : J);
+            // (with b.s and b.n of a lane past the row's end: any cell will do)
+            const int ip = p == 3 ? io : (p == 0 ? i : (g.valid ? i0 + lane : nI - 1));
+            const int I = ip >> 1, In = prolong_neighbour(ip, X.nIc);
+            const int J0 = tab(X.prow, 2 * j), J1 = tab(X.prow, 2 * j + 1);
+            pw[p][0] = tab(X.pw, 2 * j);
+            pw[p][1] = tab(X.pw, 2 * j + 1);
+            oo[p][0] = uint32_t(J0 * X.nIc + I) * S;
+            oo[p][1] = uint32_t(J0 * X.nIc + In) * S;
+            oo[p][2] = uint32_t(J1 * X.nIc + I) * S;
+            oo[p][3] = uint32_t(J1 * X.nIc + In) * S;
+        }
+    }
     const uint64_t Pb = uint64_t(L.plane) * sizeof(T);
     constexpr int Q = (2 * NS + kStageWaves - 1) / kStageWaves;
     // position of layer k in LDS
@@ -106,10 +138,32 @@ __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2))) void k_smooth_stage
             if constexpr (HAS_X) {
                 gcptr xl = layer(xin, kk, Pb);
                 rc[q] = ldb<T>(xl, b.c);
-                rw[q] = ldb<T>(xl, b.w);
-                re[q] = ldb<T>(xl, b.e);
+                if constexpr (PRO) {
+                    rw[q] = ldb<T>(xl, od);
+                } else {
+                    rw[q] = ldb<T>(xl, b.w);
+                    re[q] = ldb<T>(xl, b.e);
+                }
                 rs[q] = ldb<T>(xl, b.s);
                 rn[q] = ldb<T>(xl, b.n);
+            }
+        }
+        if constexpr (PRO) {
+            const uint64_t Pcb = uint64_t(X.nIc) * uint64_t(X.nJc) * sizeof(T);
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                gcptr cl = layer(xc, clampk(wave + q * kStageWaves, nz), Pcb);
+                auto add = [&](T v, int p) {
+                    return prolonged(v, ldb<T>(cl, oo[p][0]), ldb<T>(cl, oo[p][1]),
+                                     ldb<T>(cl, oo[p][2]), ldb<T>(cl, oo[p][3]), pw[p][0],
+                                     pw[p][1]);
+                };
+                rc[q] = add(rc[q], 0);
+                rs[q] = add(rs[q], 1);
+                rn[q] = add(rn[q], 2);
+                const T ro = add(rw[q], 3);
+                rw[q] = from_below(ro, rc[q]);
+                re[q] = from_above(ro, rc[q]);
             }
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -238,11 +292,24 @@ __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2))) void k_smooth_stage
 
 constexpr size_t kMaxLds = 160 * 1024;
 
-// The staged sweep of a small level; false where the level is not small or
-// the staging buffers do not fit in LDS.
+// Half columns that smooth_prolonged is compiled for: as many layers per
+// wavefront as keep the four points' coarse values in one or two round trips.
+// (160x96, per V-cycle with P apart and in the sweep: FP32 16 layers 134 and
+// 124 us, 40 layers 173 and 164, 48 layers 181.5 and 182; FP64 8 layers 131 and
+// 122, 16 layers 155 and 152, 24 layers 174 and 176. With 70 layers a sweep
+// that spills takes 19 us against 5.5 + 4.7.)
+template <typename T>
+constexpr int prolong_steps() { return sizeof(T) == 4 ? 20 : 8; }
+// And the blocks of it: two per CU (390 blocks of 38 layers 9.6 us against 6.7
+// + 4.9; 960 blocks 17.6 against 11.0 + 6.1).
+constexpr long long kProlongBlocks = 512;
+
+// The staged sweep of a small level (with X: of xin + P xc); false where the
+// level is not small or the staging buffers do not fit in LDS.
 template <typename T>
 bool launch_staged(const LevelView<T>& L, const T* f, const T* xin, T* xout, T omega,
-                   long long staged_columns, hipStream_t s) {
+                   const TransferView<T>* X, const T* xc, long long staged_columns,
+                   hipStream_t s) {
     if (L.plane >= staged_columns) return false;
     const int wpr = segments_per_row(L.nI);
     const int nb = L.nJ * wpr;
@@ -251,34 +318,60 @@ bool launch_staged(const LevelView<T>& L, const T* f, const T* xin, T* xout, T o
         constexpr int NS = decltype(ns)::value, G = decltype(gc)::value;
         const size_t lds = staged_lds_bytes<T>(L.nz, G);
         if (lds > kMaxLds) return;
-        auto go = [&](auto hx) {
-            constexpr bool HX = decltype(hx)::value;
-            const void* fn = reinterpret_cast<const void*>(&k_smooth_staged<T, NS, G, HX>);
+        auto go = [&](auto hx, auto pro) {
+            const auto fn = &k_smooth_staged<T, NS, G, decltype(hx)::value, decltype(pro)::value>;
             if (lds > 64 * 1024 &&
-                hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize,
                                     int(lds)) != hipSuccess) {
                 (void)hipGetLastError();
                 return;
             }
-            k_smooth_staged<T, NS, G, HX>
-                <<<nb, 64 * kStageWaves, lds, s>>>(L, f, xin, xout, omega, wpr);
+            fn<<<nb, 64 * kStageWaves, lds, s>>>(L, f, xin, xout, omega, wpr,
+                                                 X ? *X : TransferView<T>{}, xc);
             launched = true;
         };
-        if (xin) go(std::true_type{});
-        else go(std::false_type{});
+        if (X) {
+            if constexpr (NS <= prolong_steps<T>()) go(std::true_type{}, std::true_type{});
+        } else if (xin) {
+            go(std::true_type{}, std::false_type{});
+        } else {
+            go(std::false_type{}, std::false_type{});
+        }
     });
     return launched;
 }
 
 template <typename T>
+bool prolongs_in_sweep(const LevelView<T>& L, long long staged_columns) {
+    return L.plane < staged_columns && (L.nz + 1) / 2 <= prolong_steps<T>() &&
+           (long long)L.nJ * segments_per_row(L.nI) <= kProlongBlocks;
+}
+
+template <typename T>
+bool smooth_prolonged(const LevelView<T>& L, const TransferView<T>& X, const T* f, const T* xin,
+                      const T* xc, T* xout, T omega, long long staged_columns, hipStream_t s) {
+    return prolongs_in_sweep<T>(L, staged_columns) &&
+           launch_staged<T>(L, f, xin, xout, omega, &X, xc, staged_columns, s);
+}
+
+template <typename T>
 void smooth(const LevelView<T>& L, const T* f, const T* xin, T* xout, T omega,
             long long staged_columns, hipStream_t s) {
-    if (launch_staged<T>(L, f, xin, xout, omega, staged_columns, s)) return;
+    if (launch_staged<T>(L, f, xin, xout, omega, nullptr, nullptr, staged_columns, s)) return;
     sweep<T>(L, f, xin, xout, omega, s);
 }
 
 template void smooth<float>(const LevelView<float>&, const float*, const float*, float*, float,
                             long long, hipStream_t);
+template bool prolongs_in_sweep<float>(const LevelView<float>&, long long);
+template bool prolongs_in_sweep<double>(const LevelView<double>&, long long);
+template bool smooth_prolonged<float>(const LevelView<float>&, const TransferView<float>&,
+                                      const float*, const float*, const float*, float*, float,
+                                      long long, hipStream_t);
+template bool smooth_prolonged<double>(const LevelView<double>&, const TransferView<double>&,
+                                       const double*, const double*, const double*, double*,
+                                       double, long long, hipStream_t);
 template void smooth<double>(const LevelView<double>&, const double*, const double*, double*,
                              double, long long, hipStream_t);
 

@@ -304,7 +304,7 @@ __global__ __launch_bounds__(kBlock) void k_prolong_add(LevelView<T> F, Transfer
     const int J0 = tab(X.prow, 2 * j), J1 = tab(X.prow, 2 * j + 1);
     const T w0 = tab(X.pw, 2 * j), w1 = tab(X.pw, 2 * j + 1);
     const int I = i >> 1;
-    const int In = (i & 1) ? (I + 1 == nIc ? 0 : I + 1) : (I == 0 ? nIc - 1 : I - 1);
+    const int In = prolong_neighbour(i, nIc);
     constexpr uint32_t S = sizeof(T);
     const uint32_t o0 = uint32_t(J0 * nIc + I) * S, o0n = uint32_t(J0 * nIc + In) * S;
     const uint32_t o1 = uint32_t(J1 * nIc + I) * S, o1n = uint32_t(J1 * nIc + In) * S;
@@ -312,14 +312,13 @@ __global__ __launch_bounds__(kBlock) void k_prolong_add(LevelView<T> F, Transfer
     const uint64_t Pb = uint64_t(F.plane) * S, Pcb = uint64_t(nIc) * X.nJc * S;
     constexpr int NL = prolong_layers<T>();
     const int nz = F.nz, k0 = ch * NL;
-    const T a = T(0.75), b = T(0.25);
     T v[NL];
 #pragma unroll
     for (int d = 0; d < NL; ++d) {
         const int kk = clampk(k0 + d, nz);
         gcptr ck = layer(xc, kk, Pcb);
-        v[d] = ldb<T>(layer(x, kk, Pb), ox) + w0 * (a * ldb<T>(ck, o0) + b * ldb<T>(ck, o0n)) +
-               w1 * (a * ldb<T>(ck, o1) + b * ldb<T>(ck, o1n));
+        v[d] = prolonged(ldb<T>(layer(x, kk, Pb), ox), ldb<T>(ck, o0), ldb<T>(ck, o0n),
+                         ldb<T>(ck, o1), ldb<T>(ck, o1n), w0, w1);
     }
 #pragma unroll
     for (int d = 0; d < NL; ++d)

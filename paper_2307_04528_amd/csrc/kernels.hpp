@@ -66,6 +66,15 @@ template <typename T>
 void smooth(const LevelView<T>& L, const T* f, const T* xin, T* xout, T omega,
             long long staged_columns, hipStream_t s);
 
+// One staged sweep from xin + P xc (the first after a coarse-grid
+// correction) on small levels of few layers (prolongs_in_sweep; false,
+// launching nothing, elsewhere).
+template <typename T>
+bool prolongs_in_sweep(const LevelView<T>& L, long long staged_columns);
+template <typename T>
+bool smooth_prolonged(const LevelView<T>& L, const TransferView<T>& X, const T* f, const T* xin,
+                      const T* xc, T* xout, T omega, long long staged_columns, hipStream_t s);
+
 // The same sweep with the kernel for levels that fill the GPU (k_sweep.hip),
 // which smooth() uses on every level it does not stage.
 template <typename T>

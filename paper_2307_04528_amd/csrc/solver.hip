@@ -447,11 +447,11 @@ bool sweeps_in_pairs(const mg_handle* h, int l) {
 }
 
 // nu sweeps on level l with the damping factors of a smoothing step of nu
-// sweeps (reversed: in reverse order), from zero or from the iterate in cur;
-// the result is in cur.
+// sweeps (reversed: in reverse order), from zero or from the iterate in cur
+// (with xc: cur + P xc, where mgk::prolongs_in_sweep()); the result is in cur.
 template <typename T>
 mg_status smooth_run(mg_handle* h, int l, const T* f, T*& cur, T*& nxt, int nu, bool from_zero,
-                     bool reversed) {
+                     bool reversed, const T* xc = nullptr) {
     DevLevel& d = h->lv[l];
     auto om = [&](int k) { return mgs::sweep_omega(h->opt, nu, reversed ? nu - 1 - k : k); };
     const bool pairs = sweeps_in_pairs<T>(h, l);
@@ -474,6 +474,20 @@ mg_status smooth_run(mg_handle* h, int l, const T* f, T*& cur, T*& nxt, int nu, 
                 k += 2;
                 continue;
             }
+        }
+        if (xc && k == 0) {
+            const DevLevel& c = h->lv[l + 1];
+            bool done = false;
+            {
+                Launch g(h, MG_K_SMOOTH, l, (double(d.n) * 4 + double(c.n)) * sizeof(T));
+                done = mgk::smooth_prolonged<T>(view<T>(d), xview<T>(d, c), f, cur, xc, nxt,
+                                                T(om(k)), h->opt.staged_columns, h->stream);
+            }
+            MG_TRY(check_launch(h, "smooth_prolonged"));
+            if (!done) return fail(h, MG_ERR_HIP, "the sweep with prolongation was not launched");
+            std::swap(cur, nxt);
+            ++k;
+            continue;
         }
         MG_TRY(op_smooth<T>(h, l, f, xin, xout, zero ? MG_K_SMOOTH0 : MG_K_SMOOTH, om(k)));
         if (!zero) std::swap(cur, nxt);
@@ -572,10 +586,13 @@ mg_status vcycle(mg_handle* h, int l, const T* f, T** result) {
     MG_TRY(op_restrict<T>(h, l, f, cur, wc.f));
     T* xc = nullptr;
     MG_TRY(vcycle<T>(h, l + 1, wc.f, &xc));
-    MG_TRY(op_prolong<T>(h, l, xc, cur));
+    // the correction: added by the first post-sweep on small levels
+    const bool with_sweep =
+        nu2 > 0 && mgk::prolongs_in_sweep<T>(view<T>(d), h->opt.staged_columns);
+    if (!with_sweep) MG_TRY(op_prolong<T>(h, l, xc, cur));
     {
         SweepGroup g(h, l, nu2, sweeps_bytes<T>(h, l, nu2));
-        MG_TRY(smooth_run<T>(h, l, f, cur, nxt, nu2, false, false));
+        MG_TRY(smooth_run<T>(h, l, f, cur, nxt, nu2, false, false, with_sweep ? xc : nullptr));
     }
     *result = cur;
     return MG_OK;

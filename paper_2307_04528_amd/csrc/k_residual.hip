@@ -387,8 +387,8 @@ __global__ __launch_bounds__(kBlock) void k_fine_mass(LevelView<double> L,
 // levels: a column's two halves are two lanes' work (wavefronts 0 and 1 of a
 // block of 64 columns), each step has one division (the quotient Tr g / (Tr + g)
 // of a layer takes the stored inverse of the layer before), and the masses of
-// the next layers are loaded ahead. 9 us per level against 37 with one lane
-// per column and two divisions per layer.
+// the next layers are loaded ahead. 21 us per small level of 70 layers against
+// 40 with one lane per column and two divisions per layer.
 __global__ __launch_bounds__(128) void k_pivots(LevelView<double> L,
                                                 double* __restrict__ invp64,
                                                 float* __restrict__ invp32,

@@ -31,8 +31,8 @@
 // block reaches both in every phase, whatever its role.
 //
 // What bounds it: on 1024x768x70 a launch takes 261 us (single sweeps: 2 x
-// 191) and 203 us from zero (120 + 191), at 1.09 and 0.79 GB of counted
-// traffic, 4.2 and 3.9 TB/s; the rows' misaligned ends cost 1.25x the bytes
+// 191) and 195 us from zero (120 + 191), at 1.11 and 0.81 GB of counted
+// traffic, 4.2 TB/s; the rows' misaligned ends cost 1.25x the bytes
 // of f and the pivots, and without its loads a launch takes 141 us. Measured
 // on the way: three pairs that keep the next row in a second set of registers
 // 305 us, non-temporal hints 291 us, the step records as scalar loads of the
@@ -57,7 +57,7 @@ struct Strips {
 };
 
 // LDS values of a block: the ring, the edge columns (from an iterate), the
-// meeting exchange of the three pairs and the rows' step records.
+// meeting exchange of the pairs and the zeros.
 inline size_t pair_lds_values(int nz, bool zero) {
     return size_t(zero ? 4 : kSlots) * size_t(nz) * 64 + (zero ? 0 : size_t(kSlots) * kEdgeRow) +
            kPairs * 4 * 64 + kZeros;
@@ -387,7 +387,7 @@ inline Strips strips_of(int nI, int nJ) {
 }  // namespace
 
 bool sweep_pair_fits(const LevelView<float>& L, size_t max_lds) {
-    return L.nz >= 14 && L.nz <= 72 && L.nI >= 4 && L.plane >= kPairColumns &&
+    return L.nz >= 17 && L.nz <= 72 && L.nI >= 4 && L.plane >= kPairColumns &&
            pair_lds_values(L.nz, false) * sizeof(float) <= max_lds;
 }
 
@@ -417,8 +417,7 @@ bool sweep_pair(const LevelView<float>& L, const float* f, const float* xin, flo
     };
     const int half = (L.nz + 1) / 2;
     using std::integral_constant;
-    if (half <= 8) by_start(integral_constant<int, 8>{}, integral_constant<int, 4>{});
-    else if (half <= 12) by_start(integral_constant<int, 12>{}, integral_constant<int, 4>{});
+    if (half <= 12) by_start(integral_constant<int, 12>{}, integral_constant<int, 4>{});
     else if (half <= 16) by_start(integral_constant<int, 16>{}, integral_constant<int, 4>{});
     else if (half <= 20) by_start(integral_constant<int, 20>{}, integral_constant<int, 4>{});
     else if (half <= 24) by_start(integral_constant<int, 24>{}, integral_constant<int, 4>{});

@@ -1,11 +1,12 @@
 """GPU parity of two sweeps in one pass over memory (FP32 levels of at least
-98,304 columns and 14 to 72 layers): V-cycles whose finest level does its
+98,304 columns and 17 to 72 layers): V-cycles whose finest level does its
 sweeps in pairs against the same cycles with single staged sweeps, element by
 element, and against the oracle. The shells lie where the pair kernel can go
 wrong: strips that divide a row evenly, raggedly and with one strip more than
 whole segments need; rows narrower than a strip; few rows per band; a last
 band with few rows; odd layer counts and the edges of the compiled half
-columns (14, 16, 17, 40, 41, 72). V(2,2) runs pairs from zero and from an
+columns (17, 24, 25, 40, 41, 72) and below the first (14, 15, 16: single
+sweeps). V(2,2) runs pairs from zero and from an
 iterate, V(3,3) pairs and a single sweep, and the transposed cycle the factors
 reversed.
 
@@ -23,7 +24,8 @@ from gpu_util import log, t, n, solver_for, rel2, rel_inf, opts_of
 pytestmark = pytest.mark.gpu
 
 SHELLS = [(512, 256, 14), (512, 258, 16), (496, 268, 17), (620, 216, 40), (1024, 130, 41),
-          (1100, 120, 24), (62, 1600, 15), (8, 12288, 16), (480, 208, 72)]
+          (1100, 120, 24), (62, 1600, 15), (8, 12288, 16), (480, 208, 72),
+          (62, 1600, 19), (8, 12288, 18), (512, 258, 25)]
 
 
 @pytest.mark.parametrize("nu", [(2, 2), (3, 3)])

@@ -147,12 +147,20 @@ template <typename T>
 void inject_add(const LevelView<T>& F, const TransferView<T>& X, const T* xc, T* x,
                 hipStream_t s);
 
+// Block counters of the refinement step: one of the groups of blocks, and one
+// per group, a cache line apart.
+constexpr unsigned kDoneGroup = 64, kDoneStride = 32;
+inline size_t done_values(int blocks) {
+    return size_t(kDoneStride) * (1 + (size_t(blocks) + kDoneGroup - 1) / kDoneGroup);
+}
+
 // Refinement step on the finest level, in the iterate's precision TU (FP64;
 // FP32 in the pure single-precision solve):
 //   unew = uin + e (or uin when e == nullptr), written to uout if set;
 //   r = b - H unew, stored as TR; the sums of r^2 (and of b^2 when partials_b
 //   is not null) in FP64 into norms[0] (norms[1]), host memory, through
-//   per-block partial sums; *done counts the blocks (0 before and after).
+//   per-block partial sums; done counts the blocks (done_values(blocks) values,
+//   0 before and after).
 // uin == nullptr stands for a zero iterate (a solve from u = 0): it is not
 // read, and with e == nullptr as well the step is r = b.
 // Returns the number of blocks (partials written): at most

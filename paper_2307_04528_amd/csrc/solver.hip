@@ -1054,7 +1054,8 @@ mg_status build(mg_handle* h, const double* alpha) {
                                  mgk::blocks_for(f.plane), 8192});
     MG_TRY(dalloc(h, &h->partials, 2 * size_t(h->max_partials)));
     MG_TRY(dalloc(h, &h->scalar, 2));
-    MG_TRY(upload(h, &h->blocks_done, std::vector<unsigned>(1, 0u)));
+    MG_TRY(upload(h, &h->blocks_done,
+                  std::vector<unsigned>(mgk::done_values(h->max_partials), 0u)));
     MG_TRY(dalloc(h, &h->u_alt, f.n));
     MG_TRY(dalloc(h, &h->u_alt2, f.n));
     HIP_TRY(h, hipHostMalloc((void**)&h->host_scalar, 2 * sizeof(double), hipHostMallocDefault));

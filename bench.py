@@ -391,6 +391,9 @@ def main():
     # class they timed (the sweep), else from the breakdown solve
     k = kernel_roofline(stats, dom) or kern[dom]
     traffic, traffic_note = measured_traffic(sh.name, dom)
+    if traffic is not None and dom == "smooth":
+        # counted at 16 B per cell and launch; a launch may be two sweeps here
+        traffic = round(traffic * k["bytes_per_launch"] / (16 * sh.n))
     out["roofline"] = {"bound": "hbm", "kernel_class": dom, "achieved": k["GBps"],
                        "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                        "frac": k["GBps"] / HBM_PEAK_GBPS, "traffic": traffic,

@@ -20,8 +20,8 @@ constexpr int kResidualSync = 4;
 // launch against 4-row tiles without the barrier.
 constexpr int kResidualTallBlocks = 512;
 constexpr int kResidualTallRows = 16;
-// The walking refinement step: a range of layers per wavefront (the whole
-// column of the 70-layer workloads; 16 layers on shallow levels), the
+// The walking refinement step: a range of layers per wavefront (at most
+// kResidualRange on large levels, shorter ones on smaller levels), the
 // layers whose loads are in flight ahead of the one being computed, and the
 // same row tiles and barrier interval as above. Measured per launch on the
 // 1024x768x70 shell (mixed solve): 446 us with whole columns against 458 us
@@ -31,6 +31,14 @@ constexpr int kResidualTallRows = 16;
 // 16-row and 4-row tiles are within 1 % there; on 2560x1920x70 16-row
 // tiles take 2.78-2.90 ms against 2.99-3.07 ms (FP64: 3.54-3.59 against
 // 3.82-3.83 ms).
+//
+// A column is cut into as few ranges as that allows and these are of equal
+// length, because every XCD takes a contiguous part of the blocks: with 70 + 1
+// layers the XCDs that got the last layer of 1024x768x71 waited for the others
+// (FP64 740 us, 488 with 36 + 35). A walk ends with its range: steps for layers
+// that are not there would issue their loads all the same (1024x768, FP64: 17
+// layers 134 us against 268 with 70 steps, 38 layers 263 against 361; mixed 106
+// against 204, 211 against 266).
 constexpr int kResidualRange = 70;
 constexpr int kResidualShortRange = 8;
 constexpr int kResidualTinyRange = 4;
@@ -194,7 +202,7 @@ __device__ __forceinline__ void sum_by_last_block(const double* mine, double* pa
 //   unew = uin + e (HAS_E; written to uout), r = b - H unew (stored as TR),
 //   per-block partial sums of r^2 in FP64, and of b^2 when partials_b is set;
 // or the operator alone, r = H uin (MODE 1) or r = b - H uin (MODE 2), with no
-// sums. It walks ranges of LR layers: block b takes range
+// sums. It walks ranges of lr <= LR layers: block b takes range
 // b / tiles and the tile of R consecutive rows of one 64-column range
 // b % tiles (one wavefront per row), and each wavefront walks its layers
 // upward with the loads of the next P layers in flight, the layers below and
@@ -210,13 +218,13 @@ template <typename TU, typename TE, typename TR, bool HAS_E, bool HAS_U, int LR,
 __global__ __launch_bounds__(64 * R) void k_residual_walk(
     LevelView<TU> L, const TU* __restrict__ bv, const TU* __restrict__ uin,
     const TE* __restrict__ e, TU* __restrict__ uout, TR* __restrict__ r,
-    double* partials, double* partials_b, int wpr, int tiles, unsigned* done,
+    double* partials, double* partials_b, int wpr, int tiles, int lr, unsigned* done,
     double* norms) {
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
     const int blk = int(logical_block());
     const int rg = blk / tiles;
     const Seg g = tiled_segment(blk - rg * tiles, wave, R, L.nI, L.nJ, wpr);
-    const int nz = L.nz, kb = rg * LR;
+    const int nz = L.nz, kb = rg * lr, ke = kb + lr < nz ? kb + lr : nz;
     const uint32_t PU = uint32_t(L.plane) * sizeof(TU), PE = uint32_t(L.plane) * sizeof(TE),
                    PR = uint32_t(L.plane) * sizeof(TR);
     const rsrc_t ru = make_rsrc(HAS_U ? uin : bv, PU * uint32_t(nz)),
@@ -248,17 +256,20 @@ __global__ __launch_bounds__(64 * R) void k_residual_walk(
         TE ec, es, en, ew, ee;
         StepCoef<TU> q;
     };
-    // the loads of step t (layer kb + t, clamped); only the column itself
-    // for the layer above the range
+    // the loads of step t (layer kb + t); only the column itself for the
+    // layer above the range. Steps past the range load its last layers again
+    // (cache hits), not those of the next range.
     auto fetch = [&](int t, bool column_only) {
         Lay Q;
         if constexpr (!HAS_E) Q.ec = Q.es = Q.en = Q.ew = Q.ee = TE(0);
         if constexpr (!HAS_U) Q.uc = Q.us = Q.un = Q.uw = Q.ue = TU(0);
-        const int k = clampk(kb + t, nz);
-        const uint32_t su = uint32_t(k) * PU, se = uint32_t(k) * PE;
-        if constexpr (HAS_U) Q.uc = bld<TU>(ru, uc, su);
-        if constexpr (HAS_E) Q.ec = bld<TE>(re, ec, se);
+        const int kc = clampk(kb + t < ke ? kb + t : ke, nz);
+        const uint32_t cu = uint32_t(kc) * PU, ce = uint32_t(kc) * PE;
+        if constexpr (HAS_U) Q.uc = bld<TU>(ru, uc, cu);
+        if constexpr (HAS_E) Q.ec = bld<TE>(re, ec, ce);
         if (!column_only) {
+            const int k = kb + t < ke ? kb + t : ke - 1;
+            const uint32_t su = uint32_t(k) * PU, se = uint32_t(k) * PE;
             if constexpr (HAS_U) {
                 Q.us = bld<TU>(ru, us, su);
                 Q.un = bld<TU>(ru, un, su);
@@ -329,7 +340,7 @@ __global__ __launch_bounds__(64 * R) void k_residual_walk(
         // computed here, not sunk (with its loads) into the guarded stores
         asm volatile("" : "+v"(rv));
         const int k = kb + t;
-        if (k < nz && g.valid) {
+        if (k < ke && g.valid) {
             if constexpr (HAS_E) bst(xc, rw, uc, uint32_t(k) * PU);
             bst(TR(rv), rr, rc, uint32_t(k) * PR);
             if constexpr (MODE == 0) {
@@ -338,6 +349,7 @@ __global__ __launch_bounds__(64 * R) void k_residual_walk(
             }
         }
         um = xc;
+        if (k + 1 >= ke) break;   // the same for every wavefront of the block
         if (t % S == S - 1) __syncthreads();
     }
     if constexpr (MODE == 0) {
@@ -509,14 +521,15 @@ void apply(const LevelView<T>& L, const T* x, const T* f, T* y, hipStream_t s) {
         if (L.plane >= kApplyWalkColumns) {
             const int wpr = segments_per_row(L.nI);
             const int tiles = tiled_blocks(L.nJ, wpr, kApplyRows);
+            const int ranges = (L.nz + kApplyRange - 1) / kApplyRange;
             auto go = [&](auto fullc, auto modec) {
                 constexpr int MODE = decltype(modec)::value;
                 k_residual_walk<double, double, double, false, true, kApplyRange,
                                 kResidualAhead, kApplyRows, kResidualSync,
                                 decltype(fullc)::value, MODE>
-                    <<<tiles * ((L.nz + kApplyRange - 1) / kApplyRange), 64 * kApplyRows, 0,
-                       s>>>(L, f, x, nullptr, nullptr, y, nullptr, nullptr, wpr, tiles, nullptr,
-                       nullptr);
+                    <<<tiles * ranges, 64 * kApplyRows, 0, s>>>(
+                        L, f, x, nullptr, nullptr, y, nullptr, nullptr, wpr, tiles,
+                        (L.nz + ranges - 1) / ranges, nullptr, nullptr);
             };
             using One = std::integral_constant<int, 1>;
             using Two = std::integral_constant<int, 2>;
@@ -541,7 +554,8 @@ int residual_update(const LevelView<TU>& L, const TU* b, const TU* uin, const TE
                     TR* r, double* partials, double* partials_b, unsigned* done, double* norms,
                     hipStream_t s) {
     const int wpr = segments_per_row(L.nI);
-    const int nb = residual_update_blocks(L);
+    const int nb = residual_update_blocks(L), range = residual_walk_range(L.nI, L.nJ, L.nz);
+    const int ranges = (L.nz + range - 1) / range, lr = (L.nz + ranges - 1) / ranges;
     const bool tall = residual_tile_rows(L.nI, L.nJ) == kResidualTallRows;
     const int tiles = tiled_blocks(L.nJ, wpr, tall ? kResidualTallRows : 4);
     const bool full = L.nI % 64 == 0;
@@ -552,21 +566,20 @@ int residual_update(const LevelView<TU>& L, const TU* b, const TU* uin, const TE
         if (e && uin)
             k_residual_walk<TU, TE, TR, true, true, LR, P, R, S, FULLI>
                 <<<nb, 64 * R, 0, s>>>(L, b, uin, e, uout, r, partials, partials_b, wpr, tiles,
-                                        done, norms);
+                                        lr, done, norms);
         else if (e)
             k_residual_walk<TU, TE, TR, true, false, LR, P, R, S, FULLI>
                 <<<nb, 64 * R, 0, s>>>(L, b, uin, e, uout, r, partials, partials_b, wpr, tiles,
-                                        done, norms);
+                                        lr, done, norms);
         else if (uin)
             k_residual_walk<TU, TE, TR, false, true, LR, P, R, S, FULLI>
                 <<<nb, 64 * R, 0, s>>>(L, b, uin, e, uout, r, partials, partials_b, wpr, tiles,
-                                        done, norms);
+                                        lr, done, norms);
         else   // r = b: no neighbours (the same blocks and sums as with u = 0)
             k_residual_walk<TU, TE, TR, false, false, LR, P, R, S, false>
                 <<<nb, 64 * R, 0, s>>>(L, b, uin, e, uout, r, partials, partials_b, wpr, tiles,
-                                        done, norms);
+                                        lr, done, norms);
     };
-    const int range = residual_walk_range(L.nI, L.nJ, L.nz);
     auto low = [&](auto lrc) {
         if (full) go(lrc, std::integral_constant<int, 4>{}, std::true_type{});
         else go(lrc, std::integral_constant<int, 4>{}, std::false_type{});

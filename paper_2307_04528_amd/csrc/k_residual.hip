@@ -82,12 +82,21 @@ constexpr int apply_layers() {
     return std::is_same<T, float>::value ? 2 : 4;
 }
 // In FP64 large levels take the walk of the refinement step (MODE 1 and 2) in
-// ranges of kApplyRange layers, which reads each column once per range:
-// 640x480x50 92 us against 104 for this kernel (101 with ranges of 16, 89 and
-// 358 on 1024x768x70 with whole columns), 1024x768x70 276 against 323; smaller
-// levels have too few columns for it (384x192: 45 against 41 us).
+// ranges of at most kApplyRange layers, which reads each column once per range.
+// It pays where the level's three arrays exceed the 256 MB last-level cache
+// (below that the chunks' second reads of a column are cheap) and the column
+// is long enough for its pipeline. Whole calls, this kernel against the walk:
+// 640x480x50 107 and 88 us, 1152x576x50 209 and 174, x20 95 and 88; about
+// 12M cells 1024x768x15 83 and 80, 768x384x40 83 and 78, 512x512x44 75 and 76;
+// below 1024x768x14 68 and 77, 640x640x24 66 and 69, 768x384x26 55 and 59;
+// few layers 2560x1920x9 303 and 265, x8 228 and 243, x4 128 and 149.
+// (Ranges of 16 or 50 layers on 640x480x50: 101 and 89 us a launch, 89 with 25,
+// but 358 on 1024x768x70 with whole columns. On fewer columns, 384x192x70, 45
+// us with the walk against 41.)
 constexpr int kApplyRange = 25;
 constexpr long long kApplyWalkColumns = 1LL << 18;
+constexpr long long kApplyWalkCells = 3LL << 22;
+constexpr int kApplyWalkLayers = 9;
 
 // y = H x (HAS_F = false) or y = f - H x, one lane per column and chunk of
 // apply_layers layers, in blocks of 64 columns x kApplyRows rows (grid:
@@ -518,7 +527,8 @@ __global__ __launch_bounds__(kBlock) void k_fill(T* __restrict__ out, T v, long 
 template <typename T>
 void apply(const LevelView<T>& L, const T* x, const T* f, T* y, hipStream_t s) {
     if constexpr (std::is_same<T, double>::value) {
-        if (L.plane >= kApplyWalkColumns) {
+        if (L.plane >= kApplyWalkColumns && L.nz >= kApplyWalkLayers &&
+            L.plane * L.nz >= kApplyWalkCells) {
             const int wpr = segments_per_row(L.nI);
             const int tiles = tiled_blocks(L.nJ, wpr, kApplyRows);
             const int ranges = (L.nz + kApplyRange - 1) / kApplyRange;

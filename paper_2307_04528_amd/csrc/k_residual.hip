@@ -293,7 +293,7 @@ __global__ __launch_bounds__(64 * R) void k_residual_walk(
             }
             // b and the mass are read at the cell only: non-temporal loads
             if constexpr (MODE != 1) Q.b = bld<TU, true>(rb, uc, su);
-            else Q.b = TU(0);
+            else Q.b = TU(0);   // (unused)
             if constexpr (HOP) {
                 Q.m = bld<TU, true>(rm, uc, su);
                 Q.q = step_rec(qp, size_t(k));
@@ -341,11 +341,12 @@ __global__ __launch_bounds__(64 * R) void k_residual_walk(
         TU rv = c.b;
         if constexpr (HOP) {
             const StepCoef<TU> q = c.q;
-            rv -= c.m * xc + hdiff(q.tl, q.ts, q.tn, xc, xw, xe, xs, xn) + tb * (xc - um) +
-                  q.tc * (xc - xp);
+            const TU h = c.m * xc + hdiff(q.tl, q.ts, q.tn, xc, xw, xe, xs, xn) +
+                         tb * (xc - um) + q.tc * (xc - xp);
+            if constexpr (MODE == 1) rv = h;
+            else rv -= h;
             tb = q.tc;
         }
-        if constexpr (MODE == 1) rv = -rv;   // H u (b is 0)
         // computed here, not sunk (with its loads) into the guarded stores
         asm volatile("" : "+v"(rv));
         const int k = kb + t;

@@ -62,6 +62,13 @@ def test_operator_of_large_levels(size):
     assert e < 1e-13
 
 
+def test_operator_of_zero_is_zero():
+    """Plain zeros, no negative ones, on a level that walks."""
+    S, f = handle((512, 512), 48)
+    assert not torch.signbit(S.apply(torch.zeros_like(f))).any()
+    S.close()
+
+
 def handle(plane, nz, **opts):
     from paper_2307_04528_amd import Solver
     a = torch.full((nz, plane[1], plane[0]), 100.0, dtype=torch.float64, device="cuda")

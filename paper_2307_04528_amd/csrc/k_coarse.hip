@@ -290,7 +290,10 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse_sweeps(
         for (int d = 0; d < D; ++d) rb[(NC - 1) & 1][d] = fetch_back((NC - 1) * D + d);
         __syncthreads();
         T z = (xch[H + idx] + xch[idx]) * xch[2 * H + idx];
-        if (active) {
+        // Unit vectors: every lane takes part, also those without a column, since
+        // the steps' couplings lie in the lanes of vs, which a branch here would
+        // leave out of any copy of it. Only their stores are guarded.
+        if (UNIT || active) {
 #pragma unroll
             for (int c = NC - 1; c >= 0; --c) {
                 opaque();
@@ -299,6 +302,7 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse_sweeps(
                     for (int d = 0; d < D; ++d) rb[(c - 1) & 1][d] = fetch_back((c - 1) * D + d);
                 }
                 __builtin_amdgcn_sched_barrier(0);
+                T out[D];
 #pragma unroll
                 for (int d = D - 1; d >= 0; --d) {
                     const int t = c * D + d;
@@ -313,9 +317,19 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse_sweeps(
                         else k_ = r.cn * p;
                     }
                     if (t < NS - G - 1 || t < el) z = y[t] + k_ * z;
-                    const T out = damp * z + keep * r.x;
-                    if (t < NS - G || t < ow) at(xc, offset_of(t)) = out;
+                    out[d] = damp * z + keep * r.x;
+                    if constexpr (!UNIT)
+                        if (t < NS - G || t < ow) at(xc, offset_of(t)) = out[d];
                 }
+                if constexpr (UNIT)
+                    if (active) {
+#pragma unroll
+                        for (int d = D - 1; d >= 0; --d) {
+                            const int t = c * D + d;
+                            if (t >= NS) continue;
+                            if (t < NS - G || t < ow) at(xc, offset_of(t)) = out[d];
+                        }
+                    }
                 __builtin_amdgcn_sched_barrier(0);
             }
         }

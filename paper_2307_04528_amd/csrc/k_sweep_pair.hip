@@ -304,36 +304,45 @@ void k_sweep_pair(LevelView<float> L, const float* __restrict__ f, const float* 
         float z = xm;
         float* po = ring + x1slot(r) + hb + lane;
         const uint32_t ov = uint32_t(r * nI + col) * 4u;
-        if (FIRST || (lane >= 1 && lane <= cn)) {
-            float xo[2][E];
-            auto fetch_x = [&](int c) {
-                if constexpr (HAS_X) {
+        // Every lane takes part, also those with no output column: the steps'
+        // couplings lie in the lanes of q, which a branch here would leave out of
+        // any copy of it. Only the stores are guarded, a chunk of them at a time.
+        float xo[2][E];
+        auto fetch_x = [&](int c) {
+            if constexpr (HAS_X) {
 #pragma unroll
-                    for (int d = 0; d < E; ++d) xo[c & 1][d] = pc[(c * E + d) * 64];
-                }
-            };
-            fetch_x(NE - 1);
-            Offsets soff = offsets;
+                for (int d = 0; d < E; ++d) xo[c & 1][d] = pc[(c * E + d) * 64];
+            }
+        };
+        fetch_x(NE - 1);
+        Offsets soff = offsets;
 #pragma unroll
-            for (int c = NE - 1; c >= 0; --c) {
-                soff.opaque();
-                if (c > 0) fetch_x(c - 1);
-                __builtin_amdgcn_sched_barrier(0);
+        for (int c = NE - 1; c >= 0; --c) {
+            soff.opaque();
+            if (c > 0) fetch_x(c - 1);
+            __builtin_amdgcn_sched_barrier(0);
+            float out[E];
 #pragma unroll
-                for (int d = E - 1; d >= 0; --d) {
-                    const int t = c * E + d;
-                    if (t >= NS) continue;
-                    if (t < NS - G - 1 || t < elim)
-                        z = fmaf(lane_value(q.w, t) * ir[t], z, y[t]);
-                    float out = omega * z;
-                    if constexpr (HAS_X) out = fmaf(keep, xo[c & 1][d], out);
-                    if (t < NS - G || t < own) {
-                        if constexpr (FIRST) po[t * 64] = out;
-                        else bst<false>(out, ro, ov, soff(t));
+            for (int d = E - 1; d >= 0; --d) {
+                const int t = c * E + d;
+                if (t >= NS) continue;
+                if (t < NS - G - 1 || t < elim)
+                    z = fmaf(lane_value(q.w, t) * ir[t], z, y[t]);
+                out[d] = omega * z;
+                if constexpr (HAS_X) out[d] = fmaf(keep, xo[c & 1][d], out[d]);
+                if constexpr (FIRST)
+                    if (t < NS - G || t < own) po[t * 64] = out[d];
+            }
+            if constexpr (!FIRST)
+                if (lane >= 1 && lane <= cn) {
+#pragma unroll
+                    for (int d = E - 1; d >= 0; --d) {
+                        const int t = c * E + d;
+                        if (t >= NS) continue;
+                        if (t < NS - G || t < own) bst<false>(out[d], ro, ov, soff(t));
                     }
                 }
-                __builtin_amdgcn_sched_barrier(0);
-            }
+            __builtin_amdgcn_sched_barrier(0);
         }
         __syncthreads();
     };

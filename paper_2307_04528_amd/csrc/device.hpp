@@ -372,6 +372,23 @@ inline int grid_stride_blocks(long long n) {
     return int(b < 8192 ? (b > 0 ? b : 1) : 8192);
 }
 
+// Lets a kernel be launched with lds bytes of dynamic LDS. The limit is a
+// setting of the process, and a kernel's sizes differ from level to level: it is
+// always set to the same value (all of a CU's LDS), so that no thread lowers it
+// under another's launch.
+constexpr size_t kMaxLds = 160 * 1024;
+template <typename F>
+bool allow_lds(F* kernel, size_t lds) {
+    if (lds <= 64 * 1024) return true;
+    if (lds <= kMaxLds &&
+        hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                            hipFuncAttributeMaxDynamicSharedMemorySize,
+                            int(kMaxLds)) == hipSuccess)
+        return true;
+    (void)hipGetLastError();
+    return false;
+}
+
 // Dispatch the layer-count bucket NZ >= nz at compile time.
 template <typename F>
 void with_nz(int nz, F&& fn) {

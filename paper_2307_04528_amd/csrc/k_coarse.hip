@@ -387,15 +387,9 @@ bool launch(const LevelView<T>& L, const SepView& sep, const T* f, T* x, float* 
             int sweeps, int U, int blocks, hipStream_t s) {
     constexpr bool IPREG = pivots_in_registers<T>(NS);
     const size_t lds = coarse_values<T, NS, UNIT>(L.plane, L.nJ, L.nz, U) * sizeof(T);
-    if (lds > 64 * 1024 &&
-        hipFuncSetAttribute(reinterpret_cast<const void*>(&k_coarse_sweeps<T, NS, G, IPREG, UNIT>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize,
-                            int(lds)) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    k_coarse_sweeps<T, NS, G, IPREG, UNIT>
-        <<<blocks, 2 * lanes64(L.plane * U), lds, s>>>(L, sep, f, x, x32, omega, sweeps, U);
+    const auto fn = &k_coarse_sweeps<T, NS, G, IPREG, UNIT>;
+    if (!allow_lds(fn, lds)) return false;
+    fn<<<blocks, 2 * lanes64(L.plane * U), lds, s>>>(L, sep, f, x, x32, omega, sweeps, U);
     return true;
 }
 

@@ -290,8 +290,6 @@ __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2))) void k_smooth_stage
 
 }  // namespace
 
-constexpr size_t kMaxLds = 160 * 1024;
-
 // Half columns that smooth_prolonged is compiled for: as many layers per
 // wavefront as keep the four points' coarse values in one or two round trips.
 // (160x96, per V-cycle with P apart and in the sweep: FP32 16 layers 134 and
@@ -320,13 +318,7 @@ bool launch_staged(const LevelView<T>& L, const T* f, const T* xin, T* xout, T o
         if (lds > kMaxLds) return;
         auto go = [&](auto hx, auto pro) {
             const auto fn = &k_smooth_staged<T, NS, G, decltype(hx)::value, decltype(pro)::value>;
-            if (lds > 64 * 1024 &&
-                hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    int(lds)) != hipSuccess) {
-                (void)hipGetLastError();
-                return;
-            }
+            if (!allow_lds(fn, lds)) return;
             fn<<<nb, 64 * kStageWaves, lds, s>>>(L, f, xin, xout, omega, wpr,
                                                  X ? *X : TransferView<T>{}, xc);
             launched = true;

@@ -410,13 +410,7 @@ bool sweep_pair(const LevelView<float>& L, const float* f, const float* xin, flo
     auto go = [&](auto ns, auto g, auto zero) {
         constexpr bool ZERO = decltype(zero)::value;
         auto* fn = &k_sweep_pair<decltype(ns)::value, decltype(g)::value, ZERO>;
-        if (lds > 64 * 1024 &&
-            hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
-                                hipFuncAttributeMaxDynamicSharedMemorySize,
-                                int(lds)) != hipSuccess) {
-            (void)hipGetLastError();
-            return;
-        }
+        if (!allow_lds(fn, lds)) return;
         fn<<<nb, 64 * (2 * kPairs + kLoadWaves), lds, s>>>(L, f, xin, xout, om1, om2, st);
         done = true;
     };

@@ -149,7 +149,7 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse_sweeps(
     if constexpr (UNIT) {
         const int kl = k0 + (lane < own ? lane : 0) * ks;
         const int kn = kl + ks < 0 ? 0 : clampk(kl + ks, nz);
-        vv = T(sep.v[top ? kl : kl + 1]) / sqrt(T(sep.h[kl]) * T(sep.h[kn]));
+        vv = T(sep.v[top ? kl : kl + 1]) / (sqrt(T(sep.h[kl])) * sqrt(T(sep.h[kn])));
         fu = active && col == cu + u ? T(1) / sqrt(T(sep.h[ku])) : T(0);
     }
     // not UNIT, FP32: couplings times pivots kept for the back-substitution

@@ -1072,7 +1072,11 @@ mg_status build(mg_handle* h, const double* alpha) {
         const DevLevel& c = h->lv.back();
         DenseCoarse& D = h->dense;
         D.n = c.n;
-        D.enabled = mgk::coarse_basis_fits(c.plane, c.nJ, c.nz, h->max_lds);
+        // (its unknowns are scaled by the layers' horizontal factors, proportional
+        // to K, which must not be lost in underflow)
+        const std::vector<double>& fh = h->host.levels.back().fh;
+        D.enabled = mgk::coarse_basis_fits(c.plane, c.nJ, c.nz, h->max_lds) &&
+                    *std::min_element(fh.begin(), fh.end()) > 1e-300;
         if (D.enabled) {
             const size_t nn = size_t(c.n) * size_t(c.n);
             MG_TRY(dalloc(h, &D.C64, nn));

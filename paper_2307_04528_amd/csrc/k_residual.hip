@@ -683,5 +683,6 @@ template void cast<float, double>(const float*, double*, long long, hipStream_t)
 template void cast<double, double>(const double*, double*, long long, hipStream_t);
 template void fill<float>(float*, float, long long, hipStream_t);
 template void fill<double>(double*, double, long long, hipStream_t);
+template void fill<unsigned>(unsigned*, unsigned, long long, hipStream_t);
 
 }  // namespace mgk

@@ -106,6 +106,10 @@ struct mg_handle {
     double* host_scalar = nullptr; // pinned host memory: the reduced values [2]
     hipEvent_t scalar_ready = nullptr;   // recorded after what writes host_scalar
     unsigned* blocks_done = nullptr;     // blocks of the refinement step that are done
+    long long done_count = 0;            // values of blocks_done
+    // a solve began and did not end as it should (an error on the way, or a norm
+    // that was not written): its kernels may still run, blocks_done be set
+    bool unfinished = false;
     int max_partials = 0;
     int grid_partials = 0;         // the same with one range of layers per column
     size_t max_lds = 64 * 1024;    // LDS bytes a block may use (device limit)
@@ -755,7 +759,9 @@ mg_status sync_scalar(mg_handle* h, double* out) {
 // FP32 in the pure single-precision solve) and the correction e and
 // residual r in the V-cycle's precision T.
 // Enqueues the step; its ||r||^2 (and ||b||^2 with with_bnorm, summed in the
-// same pass) is written to host_scalar by the kernel, read by finish_step.
+// same pass) is written to host_scalar by the kernel, read by finish_step. The
+// step before has been read: a norm that this one does not write is NaN there,
+// which ends the solve with MG_ERR_BREAKDOWN.
 template <typename T, typename U>
 mg_status refine_step(mg_handle* h, const U* b, const U* uin, const T* e, U* uout, T* r,
                       bool with_bnorm = false) {
@@ -765,6 +771,7 @@ mg_status refine_step(mg_handle* h, const U* b, const U* uin, const T* e, U* uou
     const double bytes =
         double(d.n) * (sizeof(U) + sizeof(T) + (uin ? sizeof(U) : 0) +
                        (uin || e ? sizeof(U) : 0) + (e ? sizeof(T) + sizeof(U) : 0));
+    h->host_scalar[0] = h->host_scalar[1] = std::numeric_limits<double>::quiet_NaN();
     {
         Phase ph(h, 1);
         {
@@ -802,6 +809,12 @@ mg_status outer(mg_handle* h, const double* b, double* u, double tol, mg_stats* 
         MG_TRY(ensure_work<T>(h));
         MG_TRY(capture_coarse<T>(h));
     }
+    if (h->unfinished) {
+        HIP_TRY(h, hipDeviceSynchronize());   // (it may have run on another stream)
+        mgk::fill<unsigned>(h->blocks_done, 0u, h->done_count, h->stream);
+        MG_TRY(check_launch(h, "fill"));
+    }
+    h->unfinished = true;
     DevLevel& d = h->lv[0];
     Work<T>& w = work<T>(d);
     auto t0 = std::chrono::steady_clock::now();
@@ -931,6 +944,7 @@ mg_status outer(mg_handle* h, const double* b, double* u, double tol, mg_stats* 
         MG_TRY(check_launch(h, "cast"));
     }
     HIP_TRY(h, hipStreamSynchronize(h->stream));
+    h->unfinished = status == MG_ERR_BREAKDOWN;
     auto t1 = std::chrono::steady_clock::now();
     if (st) {
         std::memset(st, 0, sizeof *st);
@@ -1054,8 +1068,8 @@ mg_status build(mg_handle* h, const double* alpha) {
                                  mgk::blocks_for(f.plane), 8192});
     MG_TRY(dalloc(h, &h->partials, 2 * size_t(h->max_partials)));
     MG_TRY(dalloc(h, &h->scalar, 2));
-    MG_TRY(upload(h, &h->blocks_done,
-                  std::vector<unsigned>(mgk::done_values(h->max_partials), 0u)));
+    h->done_count = (long long)mgk::done_values(h->max_partials);
+    MG_TRY(upload(h, &h->blocks_done, std::vector<unsigned>(size_t(h->done_count), 0u)));
     MG_TRY(dalloc(h, &h->u_alt, f.n));
     MG_TRY(dalloc(h, &h->u_alt2, f.n));
     HIP_TRY(h, hipHostMalloc((void**)&h->host_scalar, 2 * sizeof(double), hipHostMallocDefault));

@@ -396,6 +396,18 @@ inline Strips strips_of(int nI, int nJ) {
 }  // namespace
 
 bool sweep_pair_fits(const LevelView<float>& L, size_t max_lds) {
+    // A row takes more strips than single sweeps take segments of it, most so
+    // short rows: 2 against 1 with 64 columns, 3 against 2 with 128. Single sweeps
+    // are the faster there where they are compiled for about as many layers as
+    // there are. V(2,2) cycles of two levels, single sweeps and pairs: 64x2048
+    // with 17, 32 and 70 layers 104, 126, 232 and 109, 139, 237 us (33 and 69
+    // layers, not compiled so: 174, 258 and 145, 235); 128x768 with 24 and 70
+    // layers 95, 160 and 100, 166, 128x1024 101 (17), 212 and 100, 206.
+    const bool close = L.nz <= 32 || L.nz == 70;
+    const long long strips = strips_of(L.nI, L.nJ).count, segments = segments_per_row(L.nI);
+    if (close && (2 * strips > 3 * segments ||
+                  7 * segments * L.plane < 6 * strips * kPairColumns))
+        return false;
     return L.nz >= 17 && L.nz <= 72 && L.nI >= 4 && L.plane >= kPairColumns &&
            pair_lds_values(L.nz, false) * sizeof(float) <= max_lds;
 }

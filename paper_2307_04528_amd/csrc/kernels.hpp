@@ -82,10 +82,10 @@ void sweep(const LevelView<T>& L, const T* f, const T* xin, T* xout, T omega, hi
 
 // Two consecutive sweeps (factors om1, om2; the first from zero when xin ==
 // nullptr) in one pass, for levels of at least kPairColumns columns with 17 to
-// 72 layers (sweep_pair_fits; false, launching nothing, elsewhere). A block
-// walks a band of rows, three phases longer than the band, so a level needs
-// enough rows per CU: with 70 layers, V(2,2) cycles of two levels take
-// 431 us against 485 for single sweeps on 768x384, 180 against 189 on
+// 72 layers, but for some with short rows (sweep_pair_fits; false, launching
+// nothing, elsewhere). A block walks a band of rows, three phases longer than the
+// band, so a level needs enough rows per CU: with 70 layers, V(2,2) cycles of two
+// levels take 431 us against 485 for single sweeps on 768x384, 180 against 189 on
 // 384x288 (110,592 columns), 137 against 138 on 384x192. With 38 layers on
 // 1152x768 626 against 1046 us. Short columns leave little to share: V(2,4)
 // cycles of 1280x780 take 816 against 1049 us with 18 layers, 839 against 773

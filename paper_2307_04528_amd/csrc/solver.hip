@@ -444,7 +444,7 @@ template <typename T>
 bool sweeps_in_pairs(const mg_handle* h, int l) {
     if constexpr (std::is_same<T, float>::value) {
         const DevLevel& d = h->lv[l];
-        return d.plane >= h->opt.staged_columns && d.plane >= mgk::kPairColumns &&
+        return d.plane >= h->opt.staged_columns &&
                mgk::sweep_pair_fits(view<float>(d), h->max_lds);
     }
     return false;

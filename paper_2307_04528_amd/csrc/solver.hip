@@ -111,7 +111,7 @@ struct mg_handle {
     // that was not written): its kernels may still run, blocks_done be set
     bool unfinished = false;
     int max_partials = 0;
-    int grid_partials = 0;         // the same with one range of layers per column
+    int grid_partials = 0;         // what mg_solve_noalloc's limit on the grid counts
     size_t max_lds = 64 * 1024;    // LDS bytes a block may use (device limit)
     int device = 0;                // the GPU the handle lives on
     bool no_events = false;        // record no HIP events (mg_solve_noalloc)
@@ -1190,10 +1190,12 @@ mg_status one_vcycle(mg_handle* h, const double* f, double* x, bool transposed) 
 // library's own. Each GPU holds one copy (until the process ends); its
 // address there is looked up once, at the first mg_setup on that GPU, with
 // that GPU current. Host code uses that address, never the array's name.
-constexpr size_t kScratchDoubles = 131072 + 256;
-// Grids that need more partials than this with one range of layers per column
-// are refused.
+constexpr size_t kScratchDoubles = 131072 + 512;
+// Grids that need more partials than this are refused (8.4M columns; levels of
+// more than 72 layers are counted with one range of layers and have two at most
+// on such grids).
 constexpr size_t kScratchGrid = (65536 + 256 - 2) / 2;
+static_assert(2 * (2 * kScratchGrid) + 2 <= kScratchDoubles, "two sums, two ranges");
 __device__ __align__(256) double scratch[kScratchDoubles];
 constexpr int kMaxDevices = 64;
 double* g_scratch[kMaxDevices] = {};
@@ -1404,8 +1406,8 @@ mg_status mg_solve_noalloc(mg_handle* h, const double* rhs, double* u, double to
     const size_t need = 2 * size_t(h->max_partials) + 2;
     if (size_t(h->grid_partials) > kScratchGrid || need > kScratchDoubles)
         return fail(h, MG_ERR_ARG,
-                    "grid too large for mg_solve_noalloc: %zu scratch values needed, %zu "
-                    "available", need, kScratchDoubles);
+                    "grid too large for mg_solve_noalloc: %d partial sums needed, %zu "
+                    "available", h->grid_partials, kScratchGrid);
     const bool ready = h->opt.precision == MG_PREC_FP64 ? h->have64
                        : h->opt.precision == MG_PREC_FP32 ? (h->have32 && h->b32)
                                                           : h->have32;

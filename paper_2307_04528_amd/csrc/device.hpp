@@ -50,17 +50,14 @@ __device__ __forceinline__ uint32_t global_index() {
 __device__ __forceinline__ int clampk(int k, int nz) { return k < nz ? k : nz - 1; }
 
 // Element offsets (within one layer) of a column and of its four horizontal
-// neighbours; at a pole the missing neighbour is the cell itself. ROWU: every
-// wavefront lies inside one latitude row, so the row index is wave-uniform.
+// neighbours; at a pole the missing neighbour is the cell itself.
 struct Nb {
     uint32_t c, w, e, s, n;
     int J;
 };
 
-template <bool ROWU>
 __device__ __forceinline__ Nb neighbours(uint32_t col, int nI, int nJ) {
-    int J = int(col / uint32_t(nI));
-    if constexpr (ROWU) J = __builtin_amdgcn_readfirstlane(J);
+    const int J = int(col / uint32_t(nI));
     const int i = int(col) - J * nI;
     Nb b;
     b.J = J;

@@ -118,7 +118,7 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse_sweeps(
     const int u0 = idx / P;
     const bool active = u0 < U;
     const int u = active ? u0 : 0, col = active ? idx - u0 * P : 0;
-    const Nb b = neighbours<false>(uint32_t(col), L.nI, nJ);
+    const Nb b = neighbours(uint32_t(col), L.nI, nJ);
     const int J = b.J;
     // UNIT: the block's unit vectors are 1 in layer ku, columns cu .. cu + U - 1
     const int per_layer = UNIT ? (P + U - 1) / U : 1;
@@ -407,8 +407,8 @@ bool coarse_solve(const LevelView<T>& L, const T* f, T* x, T omega, int sweeps, 
     if (!coarse_solve_fits<T>(L.plane, L.nJ, L.nz, max_lds)) return false;
     bool done = false;
     with_half((L.nz + 1) / 2, [&](auto ns, auto g) {
-        done = launch<T, decltype(ns)::value, decltype(g)::value, false>(L, SepView{}, f, x, nullptr, omega, sweeps, 1,
-                                                     1, s);
+        done = launch<T, decltype(ns)::value, decltype(g)::value, false>(
+            L, SepView{}, f, x, nullptr, omega, sweeps, 1, 1, s);
     });
     return done;
 }
@@ -438,8 +438,8 @@ bool coarse_basis(const LevelView<double>& L, const SepView& sep, double* C, flo
     const int U = basis_vectors(L.plane, L.nJ, L.nz, max_lds);
     bool done = false;
     with_half((L.nz + 1) / 2, [&](auto ns, auto g) {
-        done = launch<double, decltype(ns)::value, decltype(g)::value, true>(L, sep, nullptr, C, C32, omega, sweeps,
-                                                         U, int((L.plane + U - 1) / U * L.nz), s);
+        done = launch<double, decltype(ns)::value, decltype(g)::value, true>(
+            L, sep, nullptr, C, C32, omega, sweeps, U, int((L.plane + U - 1) / U * L.nz), s);
     });
     return done;
 }

@@ -370,12 +370,10 @@ __global__ __launch_bounds__(64 * R) void k_residual_walk(
     }
 }
 
-// Block c sums the c-th array of partials (arrays `stride` apart) into out[c].
+// One block sums the partials into *out.
 __global__ __launch_bounds__(1024) void k_sum_partials(const double* __restrict__ p, int n,
-                                                       long long stride,
                                                        double* __restrict__ out) {
     __shared__ double red[1024];
-    p += blockIdx.x * stride;
     double acc = 0;
     for (int t = threadIdx.x; t < n; t += blockDim.x) acc += p[t];
     red[threadIdx.x] = acc;
@@ -384,7 +382,7 @@ __global__ __launch_bounds__(1024) void k_sum_partials(const double* __restrict_
         if (int(threadIdx.x) < w) red[threadIdx.x] += red[threadIdx.x + w];
         __syncthreads();
     }
-    if (threadIdx.x == 0) out[blockIdx.x] = red[0];
+    if (threadIdx.x == 0) *out = red[0];
 }
 
 // Setup: M = alpha V on the finest level; counts alpha values that are not
@@ -561,7 +559,7 @@ void apply(const LevelView<T>& L, const T* x, const T* f, T* y, hipStream_t s) {
 }
 
 template <typename TU, typename TE, typename TR>
-int residual_update(const LevelView<TU>& L, const TU* b, const TU* uin, const TE* e, TU* uout,
+void residual_update(const LevelView<TU>& L, const TU* b, const TU* uin, const TE* e, TU* uout,
                     TR* r, double* partials, double* partials_b, unsigned* done, double* norms,
                     hipStream_t s) {
     const int wpr = segments_per_row(L.nI);
@@ -604,7 +602,6 @@ int residual_update(const LevelView<TU>& L, const TU* b, const TU* uin, const TE
     else if (range == 16) high(std::integral_constant<int, 16>{});
     else if (range == kResidualShortRange) low(std::integral_constant<int, kResidualShortRange>{});
     else low(std::integral_constant<int, kResidualTinyRange>{});
-    return nb;
 }
 
 template <typename TU>
@@ -619,9 +616,8 @@ int residual_update_blocks(const LevelView<TU>& L) {
     return tiles * ((L.nz + lr - 1) / lr);
 }
 
-void sum_partials(const double* partials, int n, double* out, hipStream_t s, int count,
-                  long long stride) {
-    k_sum_partials<<<count, 1024, 0, s>>>(partials, n, stride, out);
+void sum_partials(const double* partials, int n, double* out, hipStream_t s) {
+    k_sum_partials<<<1, 1024, 0, s>>>(partials, n, out);
 }
 
 int fine_mass(const LevelView<double>& L, const double* V, const double* alpha, double* M,
@@ -658,16 +654,16 @@ void fill(T* out, T v, long long n, hipStream_t s) {
     k_fill<T><<<grid_stride_blocks(n), kBlock, 0, s>>>(out, v, n);
 }
 
-template int residual_update<double, float, float>(const LevelView<double>&, const double*,
+template void residual_update<double, float, float>(const LevelView<double>&, const double*,
                                                   const double*, const float*, double*,
                                                   float*, double*, double*, unsigned*, double*,
                                                   hipStream_t);
-template int residual_update<double, double, double>(const LevelView<double>&,
+template void residual_update<double, double, double>(const LevelView<double>&,
                                                      const double*, const double*,
                                                      const double*, double*, double*,
                                                      double*, double*, unsigned*, double*,
                                                      hipStream_t);
-template int residual_update<float, float, float>(const LevelView<float>&, const float*,
+template void residual_update<float, float, float>(const LevelView<float>&, const float*,
                                                  const float*, const float*, float*, float*,
                                                  double*, double*, unsigned*, double*,
                                                  hipStream_t);

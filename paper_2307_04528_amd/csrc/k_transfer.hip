@@ -26,11 +26,10 @@ __device__ __forceinline__ pair_t<T> ld2(gcptr base, uint32_t boff) {
 // two longitude children are adjacent, so each child row is one 2-value load;
 // the children rows, tables and transfer maps are wave-uniform. The x values
 // of the chunk's layers and the layers just outside it are loaded once.
-// Chunk depth: 7 layers for FP32 on large levels (7 divides the 70-layer
-// workloads: 185 us per finest-level launch on 1024x768x70, against 199 us
-// with 4 layers, 190 with 6 and 212 with 8); 2 elsewhere (small levels need
-// the parallelism of more chunks: 3.9 us on 18x26x38 against 4.8 with 4 and 3.7
-// with 1, 9.8 on 192x144x70 against 11.1 and 10.4).
+// Chunk depth: 2 layers (small levels need the parallelism of more chunks: 3.9
+// us on 18x26x38 against 4.8 with 4 and 3.7 with 1, 9.8 on 192x144x70 against
+// 11.1 and 10.4; with an iterate, levels of 2^15 columns and more walk, see
+// k_restrict_walk); 7 for plain sums of large FP32 levels.
 constexpr int kRestrictLayers = 2;
 constexpr int kRestrictLayersLarge32 = 7;
 template <typename T, bool HAS_X, int DL>
@@ -434,8 +433,6 @@ void restrict_residual(const LevelView<T>& F, const TransferView<T>& X, const T*
     const int wprc = segments_per_row(X.nIc);
     const int nsegc = X.nJc * wprc;
     constexpr int waves = kBlock / 64;
-    constexpr int DLS = kRestrictLayers;
-    constexpr int DLL = std::is_same<T, float>::value ? kRestrictLayersLarge32 : DLS;
     if (x && F.plane >= RestrictWalk<T>::MinColumns) {
         using C = RestrictWalk<T>;
         const int units = nsegc * ((F.nz + C::LR - 1) / C::LR);
@@ -454,17 +451,20 @@ void restrict_residual(const LevelView<T>& F, const TransferView<T>& X, const T*
             if (ntl) go(Ff{}, Tt{});
             else go(Ff{}, Ff{});
         }
-    } else if (F.plane >= kSmallLevelColumns) {
-        const int units = nsegc * ((F.nz + DLL - 1) / DLL);
-        const int nb = (units + waves - 1) / waves;
-        if (x) k_restrict_seg<T, true, DLL><<<nb, kBlock, 0, s>>>(F, X, f, x, fc, wprc, nsegc, units);
-        else k_restrict_seg<T, false, DLL><<<nb, kBlock, 0, s>>>(F, X, f, x, fc, wprc, nsegc, units);
-    } else {
-        const int units = nsegc * ((F.nz + DLS - 1) / DLS);
-        const int nb = (units + waves - 1) / waves;
-        if (x) k_restrict_seg<T, true, DLS><<<nb, kBlock, 0, s>>>(F, X, f, x, fc, wprc, nsegc, units);
-        else k_restrict_seg<T, false, DLS><<<nb, kBlock, 0, s>>>(F, X, f, x, fc, wprc, nsegc, units);
+        return;
     }
+    auto chunks = [&](auto has_x, auto layers) {
+        constexpr int DL = decltype(layers)::value;
+        const int units = nsegc * ((F.nz + DL - 1) / DL);
+        k_restrict_seg<T, decltype(has_x)::value, DL>
+            <<<(units + waves - 1) / waves, kBlock, 0, s>>>(F, X, f, x, fc, wprc, nsegc, units);
+    };
+    using Small = std::integral_constant<int, kRestrictLayers>;
+    using Large32 = std::integral_constant<int, kRestrictLayersLarge32>;
+    if (x) chunks(std::true_type{}, Small{});
+    else if (std::is_same<T, float>::value && F.plane >= kSmallLevelColumns)
+        chunks(std::false_type{}, Large32{});
+    else chunks(std::false_type{}, Small{});
 }
 
 template <typename T>

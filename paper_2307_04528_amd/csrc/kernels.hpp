@@ -163,22 +163,19 @@ inline size_t done_values(int blocks) {
 //   0 before and after).
 // uin == nullptr stands for a zero iterate (a solve from u = 0): it is not
 // read, and with e == nullptr as well the step is r = b.
-// Returns the number of blocks (partials written): at most
-// max(residual_update_blocks(L), blocks_for(L.plane)).
+// It has residual_update_blocks(L) blocks, hence partial sums.
 template <typename TU, typename TE, typename TR>
-int residual_update(const LevelView<TU>& L, const TU* b, const TU* uin, const TE* e, TU* uout,
+void residual_update(const LevelView<TU>& L, const TU* b, const TU* uin, const TE* e, TU* uout,
                     TR* r, double* partials, double* partials_b, unsigned* done, double* norms,
                     hipStream_t s);
-// Blocks (hence partial sums) residual_update launches for level L.
 template <typename TU>
 int residual_update_blocks(const LevelView<TU>& L);
 // Row tiles of it (blocks per range of layers).
 template <typename TU>
 int residual_tiles(const LevelView<TU>& L);
 
-// out[c] = sum of partials[c*stride + 0..n) in a fixed order, c < count.
-void sum_partials(const double* partials, int n, double* out, hipStream_t s, int count = 1,
-                  long long stride = 0);
+// *out = sum of the n partials in a fixed order.
+void sum_partials(const double* partials, int n, double* out, hipStream_t s);
 
 // Setup: M = alpha * V (fine level; not written when M is null) and
 // per-block counts of alpha values that are not finite and > 0 (as FP64

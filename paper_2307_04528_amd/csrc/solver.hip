@@ -102,8 +102,8 @@ struct mg_handle {
     double* u_alt2 = nullptr;
     float *u32a = nullptr, *u32b = nullptr, *b32 = nullptr;   // MG_PREC_FP32 solve
     double* partials = nullptr;
-    double* scalar = nullptr;      // device: reduced values [2]
-    double* host_scalar = nullptr; // pinned host memory: the reduced values [2]
+    double* scalar = nullptr;      // device: the reduced value of the alpha check
+    double* host_scalar = nullptr; // pinned host memory: reduced values [2]
     hipEvent_t scalar_ready = nullptr;   // recorded after what writes host_scalar
     unsigned* blocks_done = nullptr;     // blocks of the refinement step that are done
     long long done_count = 0;            // values of blocks_done
@@ -733,24 +733,20 @@ mg_status vcycle_adj(mg_handle* h, int l, const T* f, T** result) {
     return MG_OK;
 }
 
-// Copy the reduced scalar to the host (asynchronously; the copy's completion
-// is the event scalar_ready), and wait for it. Waiting on the event, not the
-// stream, lets work enqueued after the copy keep the GPU busy meanwhile.
-mg_status post_scalar(mg_handle* h) {
-    HIP_TRY(h, hipMemcpyAsync(h->host_scalar, h->scalar, 2 * sizeof(double),
-                              hipMemcpyDeviceToHost, h->stream));
-    HIP_TRY(h, hipEventRecord(h->scalar_ready, h->stream));
-    return MG_OK;
-}
-
+// Wait for what host_scalar[0] was last asked for (the event scalar_ready).
+// Waiting on the event, not the stream, lets work enqueued after it keep the GPU
+// busy meanwhile.
 mg_status wait_scalar(mg_handle* h, double* out) {
     HIP_TRY(h, hipEventSynchronize(h->scalar_ready));
     *out = *h->host_scalar;
     return MG_OK;
 }
 
+// The reduced scalar, through host_scalar.
 mg_status sync_scalar(mg_handle* h, double* out) {
-    MG_TRY(post_scalar(h));
+    HIP_TRY(h, hipMemcpyAsync(h->host_scalar, h->scalar, sizeof(double), hipMemcpyDeviceToHost,
+                              h->stream));
+    HIP_TRY(h, hipEventRecord(h->scalar_ready, h->stream));
     return wait_scalar(h, out);
 }
 
@@ -1061,13 +1057,13 @@ mg_status build(mg_handle* h, const double* alpha) {
         }
     }
     DevLevel& f = h->lv[0];
-    h->max_partials = std::max({mgk::residual_update_blocks(view<double>(f)),
-                                mgk::blocks_for(f.plane), 8192});
+    // (8192: the alpha check's at most)
+    h->max_partials = std::max(mgk::residual_update_blocks(view<double>(f)), 8192);
     h->grid_partials = std::max({f.nz <= 72 ? mgk::residual_update_blocks(view<double>(f))
                                             : mgk::residual_tiles(view<double>(f)),
                                  mgk::blocks_for(f.plane), 8192});
     MG_TRY(dalloc(h, &h->partials, 2 * size_t(h->max_partials)));
-    MG_TRY(dalloc(h, &h->scalar, 2));
+    MG_TRY(dalloc(h, &h->scalar, 1));
     h->done_count = (long long)mgk::done_values(h->max_partials);
     MG_TRY(upload(h, &h->blocks_done, std::vector<unsigned>(size_t(h->done_count), 0u)));
     MG_TRY(dalloc(h, &h->u_alt, f.n));
@@ -1185,17 +1181,16 @@ mg_status one_vcycle(mg_handle* h, const double* f, double* x, bool transposed) 
     return check_launch(h, "vcycle");
 }
 
-// Scratch of mg_solve_noalloc: the per-block norm partials of the
-// refinement steps and the two reduced norms, in a device array of the
-// library's own. Each GPU holds one copy (until the process ends); its
-// address there is looked up once, at the first mg_setup on that GPU, with
-// that GPU current. Host code uses that address, never the array's name.
+// Scratch of mg_solve_noalloc: the per-block norm partials of the refinement
+// steps, in a device array of the library's own. Each GPU holds one copy (until
+// the process ends); its address there is looked up once, at the first mg_setup
+// on that GPU, with that GPU current. Host code uses that address, never the array's name.
 constexpr size_t kScratchDoubles = 131072 + 512;
 // Grids that need more partials than this are refused (8.4M columns; levels of
 // more than 72 layers are counted with one range of layers and have two at most
 // on such grids).
 constexpr size_t kScratchGrid = (65536 + 256 - 2) / 2;
-static_assert(2 * (2 * kScratchGrid) + 2 <= kScratchDoubles, "two sums, two ranges");
+static_assert(2 * (2 * kScratchGrid) <= kScratchDoubles, "two sums, two ranges");
 __device__ __align__(256) double scratch[kScratchDoubles];
 constexpr int kMaxDevices = 64;
 double* g_scratch[kMaxDevices] = {};
@@ -1403,8 +1398,8 @@ mg_status mg_solve_noalloc(mg_handle* h, const double* rhs, double* u, double to
     MG_TRY(check_solve_args(h, rhs, u, tol));
     double* sp = (h->device >= 0 && h->device < kMaxDevices) ? g_scratch[h->device] : nullptr;
     if (!sp) return fail(h, MG_ERR_ARG, "no scratch address for device %d", h->device);
-    const size_t need = 2 * size_t(h->max_partials) + 2;
-    if (size_t(h->grid_partials) > kScratchGrid || need > kScratchDoubles)
+    if (size_t(h->grid_partials) > kScratchGrid ||
+        2 * size_t(h->max_partials) > kScratchDoubles)
         return fail(h, MG_ERR_ARG,
                     "grid too large for mg_solve_noalloc: %d partial sums needed, %zu "
                     "available", h->grid_partials, kScratchGrid);
@@ -1415,16 +1410,13 @@ mg_status mg_solve_noalloc(mg_handle* h, const double* rhs, double* u, double to
         return fail(h, MG_ERR_ARG, "the work buffers of this precision are not allocated");
     // run on the scratch, with no events and no profiling; restore after
     double* partials = h->partials;
-    double* scalar = h->scalar;
     const int profile = h->opt.profile;
     h->partials = sp;
-    h->scalar = sp + 2 * size_t(h->max_partials);
     h->no_events = true;
     h->no_graphs = true;
     h->opt.profile = 0;
     mg_status s = solve_in_precision(h, rhs, u, tol, st, false, h->have64);
     h->partials = partials;
-    h->scalar = scalar;
     h->no_events = false;
     h->no_graphs = false;
     h->opt.profile = profile;

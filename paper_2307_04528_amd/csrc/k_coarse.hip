@@ -173,7 +173,11 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse_sweeps(
     const uint32_t xb = uint32_t(u) * uint32_t(P) + (FIXED && top ? NS * kStride : 0);
     // UNIT: this half's step with the unit values (-1: none)
     const int tu = !UNIT ? -1 : (top ? (ku >= m ? nz - 1 - ku : -1) : (ku < m ? ku : -1));
-    const uint32_t xc = (xb + uint32_t(col)) * uint32_t(sizeof(T)),
+    // (unit vectors: a lane without a column has a place of its own beyond the
+    // columns, where the layout has one)
+    constexpr bool SPARE = UNIT && FIXED;
+    const uint32_t xc = (SPARE ? uint32_t(idx) + (top ? NS * kStride : 0) : xb + uint32_t(col)) *
+                        uint32_t(sizeof(T)),
                    xw = (xb + b.w) * uint32_t(sizeof(T)), xe = (xb + b.e) * uint32_t(sizeof(T)),
                    xs = (xb + b.s) * uint32_t(sizeof(T)), xn = (xb + b.n) * uint32_t(sizeof(T));
     auto at = [&](uint32_t base, uint32_t off) -> T& {
@@ -292,7 +296,7 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse_sweeps(
         T z = (xch[H + idx] + xch[idx]) * xch[2 * H + idx];
         // Unit vectors: every lane takes part, also those without a column, since
         // the steps' couplings lie in the lanes of vs, which a branch here would
-        // leave out of any copy of it. Only their stores are guarded.
+        // leave out of any copy of it. Only stores are guarded (none with SPARE).
         if (UNIT || active) {
 #pragma unroll
             for (int c = NC - 1; c >= 0; --c) {
@@ -318,10 +322,10 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse_sweeps(
                     }
                     if (t < NS - G - 1 || t < el) z = y[t] + k_ * z;
                     out[d] = damp * z + keep * r.x;
-                    if constexpr (!UNIT)
+                    if constexpr (!UNIT || SPARE)
                         if (t < NS - G || t < ow) at(xc, offset_of(t)) = out[d];
                 }
-                if constexpr (UNIT)
+                if constexpr (UNIT && !SPARE)
                     if (active) {
 #pragma unroll
                         for (int d = D - 1; d >= 0; --d) {

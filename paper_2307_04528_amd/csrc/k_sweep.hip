@@ -109,7 +109,7 @@ void k_sweep(LevelView<T> L, const T* __restrict__ f, const T* __restrict__ xin,
     // (measured: 1-2% faster solves with it than with the hint)
     constexpr bool NT_STORE = CP >= 1 && (HAS_X || !std::is_same<T, float>::value);
     constexpr bool NT_LOAD = CP >= 2;
-    static_assert(NS <= (NZ <= 72 ? 72 : 136), "step table too short");
+    static_assert(NS <= 72, "step table too short");
     // the meeting exchange of each pair
     __shared__ T xch[kSweepPairs][4][64];
 

@@ -13,12 +13,12 @@ namespace mgk {
 // Tth[k][J+1], and tc, the vertical coupling to the next layer in that
 // direction (Tr[k+1][J] upward, Tr[k][J] downward). Table layout
 // [dir][J][t], step_stride(nz) records per row: as many as the layers, and
-// as the padded steps of the compiled sweeps reach.
+// as the padded steps of the compiled sweeps and their lanes reach (64).
 template <typename T>
 struct alignas(4 * sizeof(T)) StepCoef {
     T tl, ts, tn, tc;
 };
-inline int step_stride(int nz) { return nz <= 72 ? 72 : 136; }
+inline int step_stride(int nz) { return nz <= 72 ? 72 : (nz + 7) / 8 * 8; }
 
 // Geometry and operator data of one level, in the precision T of the kernels
 // that read it. Fields are [k][J][i] with i fastest; plane = nI*nJ.

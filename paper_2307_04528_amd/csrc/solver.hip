@@ -51,7 +51,7 @@ struct DevLevel {
     float *Tlam32 = nullptr, *Tth32 = nullptr, *Tr32 = nullptr;
     double *M64 = nullptr, *invp64 = nullptr;
     float *M32 = nullptr, *invp32 = nullptr;
-    double *fh = nullptr, *fv = nullptr, *flam = nullptr, *fth = nullptr, *fr = nullptr;
+    mgk::SepView sep;   // (the coarsest level's matrix)
     mgk::StepCoef<double>* sc64 = nullptr;
     mgk::StepCoef<float>* sc32 = nullptr;
     // to the next coarser level
@@ -968,8 +968,8 @@ mg_status rebuild_dense(mg_handle* h) {
     D.valid = false;
     if (!D.enabled) return MG_OK;
     const DevLevel& c = h->lv.back();
-    if (!mgk::coarse_basis(view<double>(c), {c.fh, c.fv, c.flam, c.fth, c.fr}, D.C64, D.C32,
-                           h->opt.omega, h->opt.coarse_sweeps, h->max_lds, h->stream)) {
+    if (!mgk::coarse_basis(view<double>(c), c.sep, D.C64, D.C32, h->opt.omega,
+                           h->opt.coarse_sweeps, h->max_lds, h->stream)) {
         D.enabled = false;   // does not fit: keep the sweeps
         return MG_OK;
     }
@@ -1035,13 +1035,6 @@ mg_status build(mg_handle* h, const double* alpha) {
         MG_TRY(dalloc(h, &d.invp64, d.n));
         MG_TRY(dalloc(h, &d.M32, d.n));
         MG_TRY(dalloc(h, &d.invp32, d.n));
-        if (l + 1 == L) {   // the coarsest level's matrix
-            MG_TRY(upload(h, &d.fh, s.fh));
-            MG_TRY(upload(h, &d.fv, s.fv));
-            MG_TRY(upload(h, &d.flam, s.flam));
-            MG_TRY(upload(h, &d.fth, s.fth));
-            MG_TRY(upload(h, &d.fr, s.fr));
-        }
         if (l + 1 < L) {
             MG_TRY(upload(h, &d.crow_of, s.crow_of));
             MG_TRY(upload(h, &d.prow, s.prow));
@@ -1065,7 +1058,9 @@ mg_status build(mg_handle* h, const double* alpha) {
     MG_TRY(dalloc(h, &h->partials, 2 * size_t(h->max_partials)));
     MG_TRY(dalloc(h, &h->scalar, 1));
     h->done_count = (long long)mgk::done_values(h->max_partials);
-    MG_TRY(upload(h, &h->blocks_done, std::vector<unsigned>(size_t(h->done_count), 0u)));
+    MG_TRY(dalloc(h, &h->blocks_done, size_t(h->done_count)));
+    mgk::fill<unsigned>(h->blocks_done, 0u, h->done_count, h->stream);
+    MG_TRY(check_launch(h, "fill"));
     MG_TRY(dalloc(h, &h->u_alt, f.n));
     MG_TRY(dalloc(h, &h->u_alt2, f.n));
     HIP_TRY(h, hipHostMalloc((void**)&h->host_scalar, 2 * sizeof(double), hipHostMallocDefault));
@@ -1079,18 +1074,25 @@ mg_status build(mg_handle* h, const double* alpha) {
         (void)hipGetLastError();
     }
     {
-        const DevLevel& c = h->lv.back();
+        DevLevel& c = h->lv.back();
+        const mgs::Level& s = h->host.levels.back();
         DenseCoarse& D = h->dense;
         D.n = c.n;
         // (its unknowns are scaled by the layers' horizontal factors, proportional
         // to K, which must not be lost in underflow)
-        const std::vector<double>& fh = h->host.levels.back().fh;
         D.enabled = mgk::coarse_basis_fits(c.plane, c.nJ, c.nz, h->max_lds) &&
-                    *std::min_element(fh.begin(), fh.end()) > 1e-300;
+                    *std::min_element(s.fh.begin(), s.fh.end()) > 1e-300;
         if (D.enabled) {
             const size_t nn = size_t(c.n) * size_t(c.n);
             MG_TRY(dalloc(h, &D.C64, nn));
             MG_TRY(dalloc(h, &D.C32, nn));
+            std::vector<double> all;   // the five arrays in one
+            const double** at[] = {&c.sep.h, &c.sep.v, &c.sep.gl, &c.sep.gt, &c.sep.gr};
+            const std::vector<double>* from[] = {&s.fh, &s.fv, &s.flam, &s.fth, &s.fr};
+            for (const auto* f : from) all.insert(all.end(), f->begin(), f->end());
+            double* p = nullptr;
+            MG_TRY(upload(h, &p, all));
+            for (int i = 0; i < 5; p += from[i++]->size()) *at[i] = p;
         }
     }
     return set_coeffs(h, alpha);

@@ -53,13 +53,33 @@ constexpr size_t staged_lds_bytes(int nz, int pad) {
     return sizeof(T) * (2 * size_t(nz + pad) * 64 + 256);
 }
 
+// Whether the couplings times pivots for the way back are kept in registers
+// (else formed again), and the wavefronts per SIMD that the registers must allow.
+// FP32: two blocks per CU, 128 VGPRs (26 us against 34 with one on 51,200 columns
+// of 100 layers). FP64 spills at 128: 20.7 us against 19.1 on 23,552 columns of
+// 70 layers. From zero it has fewer values to hold, and more blocks per CU pay on
+// the larger levels: two from 49 to 72 layers without the kept products (320x200
+// columns of 70 layers 28.0 -> 23.7 us, 200x128 16.3 -> 13.3; 3,072 columns 8.4 ->
+// 8.6), four from 17 to 32 (320x200x24 12.4 -> 10.5, x32 14.1 -> 12.3); between,
+// LDS holds two either way.
+template <typename T, int NS, bool HAS_X>
+constexpr bool kept_couplings() {
+    if (sizeof(T) == 4) return NS <= 44;
+    return HAS_X ? NS <= 36 : NS <= 8 || (NS > 16 && NS <= 24);
+}
+template <typename T, int NS, bool HAS_X>
+constexpr int staged_waves() {
+    if (sizeof(T) == 4) return 4;
+    return HAS_X || NS > 36 ? 2 : (NS <= 16 ? 8 : (NS <= 24 ? 2 : 4));
+}
+
 // NS: steps of a half column compiled for; a half has more than NS - G.
 // PRO: the iterate is xin + P xc, formed as it is loaded: the first sweep after
 // a coarse-grid correction, without a launch of its own for P (4.7 us on any
 // small level; FP32 sweeps of 38 layers take 6.9 us instead of 4.8).
 template <typename T, int NS, int G, bool HAS_X, bool PRO>
 __global__ __launch_bounds__(64 * kStageWaves)
-__attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2))) void k_smooth_staged(
+__attribute__((amdgpu_waves_per_eu(staged_waves<T, NS, HAS_X>()))) void k_smooth_staged(
     LevelView<T> L, const T* __restrict__ f, const T* __restrict__ xin, T* __restrict__ xout,
     T omega, int wpr, TransferView<T> X, const T* __restrict__ xc) {
     // products and sums are contracted by hand: the same bits in every variant
@@ -187,11 +207,7 @@ __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2))) void k_smooth_stage
     const int own = top ? elim + 1 : elim;   // and the layers it solves for
     T* hs = ls + (top ? m * 64 : 0) + lane;
     const T* hp = lp + (top ? m * 64 : 0) + lane;
-    // Couplings times pivots for the way back, kept where the registers allow.
-    // (FP32: two blocks per CU, 128 VGPRs: 26 us against 34 with one on the
-    // 51,200 columns of 100 layers. FP64 spills at 128: 20.7 us against 19.1
-    // on 23,552 columns of 70 layers.)
-    constexpr bool KEEPCB = sizeof(T) == 4 ? NS <= 44 : NS <= 36;
+    constexpr bool KEEPCB = kept_couplings<T, NS, HAS_X>();
     constexpr int D = sizeof(T) == 4 ? 6 : 3;
     constexpr int NC = (NS + D - 1) / D;
     T y[NS], cb[KEEPCB ? NS : 1];

@@ -1,9 +1,10 @@
 """GPU parity where a wavefront has few lanes with a column of their own: pairs of
-sweeps whose last strip is 2 or 3 columns wide (3722 = 60 strips of 62 and 2, and
-3782 + 2 columns: 62 strips of 61 and one of 2), and the coarsest level's sweeps
-and explicit matrix with a last wavefront of 2 to 24 lanes (66 and 130 columns, 3
-unit vectors of 72). The other lanes still hold the steps' vertical couplings,
-which all lanes read.
+sweeps whose last strip is 2 columns wide (3722 and 3784 columns: 60 and 61 strips
+of 62 before it), and the coarsest level's solve with a last wavefront of 4 lanes
+(132 columns, swept in LDS) and of 8, 12 and 24 (unit vectors side by side: 2 of 100
+columns, 3 of 68 and of 72, the iterate at a fixed stride and, with 80 layers, by
+layer). The other lanes still hold the steps' vertical couplings, which all lanes
+read.
 
 Tolerances as for any FP32 cycle (1e-4 in the 2-norm) and, in FP64, 1e-12 of the
 largest value.
@@ -34,7 +35,7 @@ def test_pairs_on_a_narrow_last_strip(size):
 
 
 @pytest.mark.parametrize("prec", ["fp64", "mixed"])
-@pytest.mark.parametrize("size", [(6, 12, 40), (22, 6, 20), (10, 26, 9), (66, 2, 30), (26, 10, 70)],
+@pytest.mark.parametrize("size", [(6, 12, 40), (22, 6, 20), (34, 2, 30), (10, 10, 61), (34, 2, 80)],
                          ids=lambda s: "x".join(map(str, s)))
 def test_coarsest_solve_with_a_narrow_last_wavefront(size, prec):
     sh = shellgen.Shell("narrow", *size, stretch=1.02)
